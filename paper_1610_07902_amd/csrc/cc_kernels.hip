@@ -8,27 +8,14 @@
 //   joins the next x (when it has out-edges); stop when x is empty.
 // At the fixed point label(v) = the smallest vertex that reaches v (for a
 // symmetric A, the smallest vertex of v's component).  Only the entries of
-// the current x and y are touched per step; x is appended in any order
-// (one counter update per wave).
+// the current x and y are touched per step; x is appended tile by tile in
+// any order (one counter update per tile).
 
-#include "internal.h"
+#include "device_ops.h"
 
 namespace spv {
 
 namespace {
-
-__device__ __forceinline__ void append(bool take, int32_t j, int32_t v, int32_t* x_idx, int32_t* x_val, Ctrl* ctrl) {
-    const int lane = threadIdx.x & 63;
-    const uint64_t vote = __ballot(take);
-    int32_t first = 0;
-    if (lane == 0 && vote) first = atomicAdd(&ctrl->gen_count, (int32_t)__popcll(vote));
-    first = __shfl(first, 0, 64);
-    if (take) {
-        const int p = first + (int)__popcll(vote & ((1ull << lane) - 1ull));
-        x_idx[p] = j;
-        x_val[p] = v;
-    }
-}
 
 __global__ void k_cc_reset(Ctrl* ctrl) {
     if (threadIdx.x == 0) {
@@ -36,61 +23,67 @@ __global__ void k_cc_reset(Ctrl* ctrl) {
         ctrl->level = 0;
         ctrl->gen_count = 0;
         ctrl->nnz_y = 0;
+        ctrl->step_done = 0;
     }
 }
 
-__global__ void k_cc_init(int32_t n, const int32_t* colptr, int32_t* label, int32_t* x_idx, int32_t* x_val,
-                          Ctrl* ctrl) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x; b < n; b += stride) {
-        const int64_t v = b + threadIdx.x;
-        bool take = false;
-        if (v < n) {
-            label[v] = (int32_t)v;
-            take = colptr[v + 1] > colptr[v];
+// Both kernels are bound by memory; x takes one counter update per tile
+// (append_tile, measured on the PageRank step).
+__global__ __launch_bounds__(kStepBlock) void k_cc_init(int32_t n, const int32_t* colptr, int32_t* label,
+                                                        int32_t* x_idx, uint32_t* x_val, Ctrl* ctrl) {
+    __shared__ int s_cnt[kWave];
+    for (int64_t b = (int64_t)blockIdx.x * kStepTile; b < n; b += (int64_t)gridDim.x * kStepTile) {
+        int32_t j[kStepItems];
+        uint32_t v[kStepItems];
+        bool take[kStepItems];
+#pragma unroll
+        for (int i = 0; i < kStepItems; ++i) {
+            const int64_t p = b + i * kStepBlock + threadIdx.x;
+            j[i] = (int32_t)(p < n ? p : n - 1);
+            v[i] = (uint32_t)j[i];
+            take[i] = colptr[j[i] + 1] > colptr[j[i]] && p < n;
         }
-        append(take, (int32_t)v, (int32_t)v, x_idx, x_val, ctrl);
+#pragma unroll
+        for (int i = 0; i < kStepItems; ++i) label[j[i]] = j[i];
+        append_tile<kStepBlock, kStepItems>(take, j, v, x_idx, x_val, &ctrl->gen_count, s_cnt);
     }
+    finish_step(ctrl);
 }
 
-__global__ void k_cc_update(const int32_t* colptr, int32_t* label, const int32_t* y_idx, const int32_t* y_val,
-                            int32_t* x_idx, int32_t* x_val, Ctrl* ctrl) {
+__global__ __launch_bounds__(kStepBlock) void k_cc_update(const int32_t* colptr, int32_t* label, const int32_t* y_idx,
+                                                          const int32_t* y_val, int32_t* x_idx, uint32_t* x_val,
+                                                          Ctrl* ctrl) {
+    __shared__ int s_cnt[kWave];
     const int64_t cnt = __hip_atomic_load(&ctrl->nnz_y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int32_t f = __hip_atomic_load(&ctrl->f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int32_t f = ld_ctrl(&ctrl->f);
     if (f <= 0) return;   // the multiply was a no-op; y holds stale entries
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x; b < cnt; b += stride) {
-        const int64_t p = b + threadIdx.x;
-        bool take = false;
-        int32_t i = 0, v = 0;
-        if (p < cnt) {
-            i = y_idx[p];
-            v = y_val[p];
-            if (v < label[i]) {
-                label[i] = v;   // i appears once in y: no other thread writes it
-                take = colptr[i + 1] > colptr[i];
-            }
+    for (int64_t b = (int64_t)blockIdx.x * kStepTile; b < cnt; b += (int64_t)gridDim.x * kStepTile) {
+        int32_t j[kStepItems], y[kStepItems], old[kStepItems], len[kStepItems];
+        uint32_t v[kStepItems];
+        bool take[kStepItems];
+#pragma unroll
+        for (int i = 0; i < kStepItems; ++i) {
+            const int64_t p = b + i * kStepBlock + threadIdx.x;
+            const int64_t pc = p < cnt ? p : cnt - 1;
+            j[i] = y_idx[pc];
+            y[i] = y_val[pc];
         }
-        append(take, i, v, x_idx, x_val, ctrl);
+#pragma unroll
+        for (int i = 0; i < kStepItems; ++i) {
+            old[i] = label[j[i]];
+            len[i] = colptr[j[i] + 1] - colptr[j[i]];
+        }
+#pragma unroll
+        for (int i = 0; i < kStepItems; ++i) {
+            // j appears once in y: no other thread writes its label
+            const bool lower = b + i * kStepBlock + threadIdx.x < cnt && y[i] < old[i];
+            if (lower) label[j[i]] = y[i];
+            take[i] = lower && len[i] > 0;
+            v[i] = (uint32_t)y[i];
+        }
+        append_tile<kStepBlock, kStepItems>(take, j, v, x_idx, x_val, &ctrl->gen_count, s_cnt);
     }
-}
-
-// Next x length; counts the multiply that just ran if it had input.
-__global__ void k_cc_publish(Ctrl* ctrl) {
-    if (threadIdx.x == 0) {
-        const int32_t fp = __hip_atomic_load(&ctrl->f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int32_t nx = __hip_atomic_load(&ctrl->gen_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (fp > 0) __hip_atomic_store(&ctrl->level, ctrl->level + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&ctrl->f, nx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&ctrl->gen_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
-inline int grid_of(int64_t count) {
-    int64_t g = (count + 255) / 256;
-    if (g < 1) g = 1;
-    if (g > 4096) g = 4096;
-    return (int)g;
+    finish_step(ctrl);
 }
 
 }  // namespace
@@ -98,16 +91,15 @@ inline int grid_of(int64_t count) {
 hipError_t launch_cc_init(int32_t n, const int32_t* colptr, int32_t* label, int32_t* x_idx, int32_t* x_val,
                           Ctrl* ctrl, hipStream_t s) {
     hipLaunchKernelGGL(k_cc_reset, dim3(1), dim3(64), 0, s, ctrl);
-    hipLaunchKernelGGL(k_cc_init, dim3(grid_of(n)), dim3(256), 0, s, n, colptr, label, x_idx, x_val, ctrl);
-    hipLaunchKernelGGL(k_cc_publish, dim3(1), dim3(64), 0, s, ctrl);
+    hipLaunchKernelGGL(k_cc_init, dim3(step_grid(n)), dim3(kStepBlock), 0, s, n, colptr, label, x_idx,
+                       reinterpret_cast<uint32_t*>(x_val), ctrl);
     return hipGetLastError();
 }
 
 hipError_t launch_cc_update(int32_t n, const int32_t* colptr, int32_t* label, const int32_t* y_idx,
                             const int32_t* y_val, int32_t* x_idx, int32_t* x_val, Ctrl* ctrl, hipStream_t s) {
-    hipLaunchKernelGGL(k_cc_update, dim3(grid_of(n)), dim3(256), 0, s, colptr, label, y_idx, y_val, x_idx, x_val,
-                       ctrl);
-    hipLaunchKernelGGL(k_cc_publish, dim3(1), dim3(64), 0, s, ctrl);
+    hipLaunchKernelGGL(k_cc_update, dim3(step_grid(n)), dim3(kStepBlock), 0, s, colptr, label, y_idx, y_val, x_idx,
+                       reinterpret_cast<uint32_t*>(x_val), ctrl);
     return hipGetLastError();
 }
 

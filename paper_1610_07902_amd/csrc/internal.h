@@ -74,7 +74,8 @@ struct alignas(256) Ctrl {
     int32_t maxrow;         // longest row of A (create, with the transpose)
     int64_t aux_count;      // masked multiply: length of the masked product before the combine
     int32_t bv_f;           // bitvector call: x entries found in its bitmap
-    uint32_t pad[21];
+    uint32_t step_done;     // workgroups that finished a PageRank / label-propagation step (zero between steps)
+    uint32_t pad[20];
 };
 static_assert(sizeof(Ctrl) == 256, "Ctrl must stay 256 bytes");
 
