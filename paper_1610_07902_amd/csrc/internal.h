@@ -358,7 +358,8 @@ hipError_t launch_merge_batch(const MergeArgs& a, int semiring, int block, bool 
 // Multi-source BFS in the pull direction (msbfs_kernels.hip): frontier and
 // seen masks with one bit per source, G = ceil(nsrc / 64) 64-bit words per
 // vertex (vertex-major).
-constexpr int kMsLong = 64;   // rows longer than this are scanned by a whole wave
+constexpr int kMsLong = 256;    // rows longer than this are scanned by a whole wave
+constexpr int kMsHuge = 2048;   // rows longer than this by a whole workgroup
 struct MsArgs {
     int32_t n;
     int G;
@@ -371,11 +372,13 @@ struct MsArgs {
     int32_t* level;          // [nsrc][n]
     int32_t* parent;         // [nsrc][n], nullable
     int32_t lvl;             // level of the vertices found now
-    const int32_t* long_rows;
-    const int32_t* long_count;
-    unsigned long long* found_total;   // += bits set in fnext
+    const int32_t* long_rows;    // [long_cap] rows longer than kMsLong from the start, than kMsHuge from the end
+    int32_t long_cap;
+    const int32_t* long_count;   // [2] how many of each
+    uint64_t* found_any;         // set when the step finds a vertex
 };
-hipError_t launch_ms_long_rows(const int32_t* rowptr, int32_t n, int32_t* rows, int32_t* count, hipStream_t s);
+hipError_t launch_ms_long_rows(const int32_t* rowptr, int32_t n, int32_t* rows, int32_t cap, int32_t* count,
+                               hipStream_t s);
 hipError_t launch_ms_to_pull(const MsArgs& a, const uint32_t* visited, int32_t mask_words, const int32_t* front,
                              const int64_t* xoff, uint64_t* fm, hipStream_t s);
 hipError_t launch_ms_pull(const MsArgs& a, bool parent, int num_cu, hipStream_t s);

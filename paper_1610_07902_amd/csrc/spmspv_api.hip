@@ -2138,9 +2138,10 @@ int msbfs_diropt(spmspv_matrix* A, int semiring, int nsrc, int32_t* level, int32
     const int xmode = semiring == SR_MIN_SELECT2ND ? XV_INDEX : XV_TRUE;
     const int G = (nsrc + 63) / 64;
     const double alpha = 14.0;
+    const int32_t long_cap = (int32_t)(A->nnz / kMsLong + 2);   // the array's size in the batch layout
     if (!B.ms_long_ready) {
-        HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(long_count), 0u, 1, s));
-        HIP_TRY(launch_ms_long_rows(A->rowptr, (int32_t)A->n, reinterpret_cast<int32_t*>(B.ws + L.ms_long),
+        HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(long_count), 0u, 2, s));
+        HIP_TRY(launch_ms_long_rows(A->rowptr, (int32_t)A->n, reinterpret_cast<int32_t*>(B.ws + L.ms_long), long_cap,
                                     long_count, s));
         B.ms_long_ready = true;
     }
@@ -2184,8 +2185,9 @@ int msbfs_diropt(spmspv_matrix* A, int semiring, int nsrc, int32_t* level, int32
         ma.level = level;
         ma.parent = semiring == SR_MIN_SELECT2ND ? parent : nullptr;
         ma.long_rows = reinterpret_cast<const int32_t*>(B.ws + L.ms_long);
+        ma.long_cap = long_cap;
         ma.long_count = long_count;
-        ma.found_total = counter;
+        ma.found_any = reinterpret_cast<uint64_t*>(counter);
         ma.seen = reinterpret_cast<uint64_t*>(B.ws + L.ms_seen);
         int cf = 0;
         ma.fcur = fm[cf];

@@ -120,3 +120,28 @@ def test_full_size_rmat20_64_sources(spv):
         assert np.array_equal(lev[k], olev), f"levels of source {k}"
         assert np.array_equal(par[k], opar), f"parents of source {k}"
     M.close()
+
+
+@pytest.mark.parametrize("nsrc", [7, 64, 70])
+@pytest.mark.parametrize("semiring", [1, 2])
+def test_hub_rows_at_the_scan_limits(spv, nsrc, semiring):
+    """Hubs whose rows end at the limits between packed rows, one wave and a
+    workgroup per row (and of the workgroup's parts), searched from hubs and
+    leaves, so that other hubs' rows are scanned with few and many sources
+    left."""
+    rng = np.random.default_rng(nsrc)
+    degs = [1, 2, 63, 64, 65, 255, 256, 257, 320, 321, 576, 577, 2047, 2048, 2049, 2048 + 1024, 16384, 16385, 30011]
+    leaves = 40000
+    n = len(degs) + leaves
+    src = np.concatenate([np.full(d, h) for h, d in enumerate(degs)])
+    dst = np.concatenate([len(degs) + rng.choice(leaves, d, replace=False) for d in degs])
+    r, c = np.concatenate([src, dst]), np.concatenate([dst, src])
+    order = np.lexsort((r, c))
+    r, c = r[order], c[order]
+    A = synth.CSC(n, n, np.concatenate([[0], np.cumsum(np.bincount(c, minlength=n))]).astype(np.int32),
+                  r.astype(np.int32), None)
+    M = spv.Matrix.from_csc(A, flags=spv.SYMMETRIC, pattern=True)
+    M.attach_batch(nsrc, msbfs=True)
+    roots = [int(k % len(degs)) if k % 2 else int(dst[rng.integers(dst.size)]) for k in range(nsrc)]
+    check(spv, M, A, roots, semiring)
+    M.close()
