@@ -477,12 +477,13 @@ struct PersistArgs {
     const int32_t* colptr;
     const int32_t* rowids;
     int32_t n;               // vertices (square A): the length of every list and bitmap below
-    int32_t* front[3];       // [n] each: frontier lists of three consecutive levels; front[0] on entry and exit
+    int32_t* front[2];       // [n] each: frontier lists of two consecutive levels; front[0] on entry and exit
     uint32_t* visited;
-    uint32_t* disc[3];       // [n/32] each: discovered-at-that-level bitmaps (min-select2nd), zero between launches
-    int32_t* pmin;           // [n] smallest frontier in-neighbour (min-select2nd), INT32_MAX between launches
-    uint32_t* bar;           // [160]: arrivals, three append counters, generation, 32 words apart; zero at launch
+    uint64_t* state;         // [n] level << 32 | parent of the vertices this launch discovers (min-select2nd),
+                             // the sign bit alone between launches
+    uint32_t* bar;           // [kPersistBarWords] barrier words and append counters; zero at launch
 };
+constexpr int kPersistBarWords = 19 * 32;
 int persistent_grid(int num_cu);
 hipError_t launch_bfs_persistent(const PersistArgs& a, bool min_semiring, int grid, hipStream_t s);
 

@@ -58,7 +58,7 @@ inline int ceil_log2(int64_t v) {
 // Offsets of every region inside the caller's workspace.
 struct Layout {
     size_t ctrl, rcp, partials, cstart, coff, cxv, chunk_col, lb1, cursor, lb3, xw, xrec, buckets, visited, front0,
-        front1, front2, disc, pmin, bar, samples, gpoff, roff, gb_lb, gb_bytes, bv_idx, bv_val, bv_tiles, dc_aux, det_list,
+        front1, front2, pmin, bar, samples, gpoff, roff, gb_lb, gb_bytes, bv_idx, bv_val, bv_tiles, dc_aux, det_list,
         det_counts, det_partials, det_long, det_long_count, h_f64, h_i32, h_orbits, h_touched, total;
     // pull direction (present with SPMSPV_WITH_TRANSPOSE or SPMSPV_SYMMETRIC)
     size_t p_xbits, p_xdense, p_ybits, p_ydense, p_lbp, p_part, p_chain, t_colids, t_values, selector;
@@ -113,9 +113,8 @@ Layout make_layout(int64_t m, int64_t n, int64_t nnz, int flags = 0, int64_t dc_
     L.front0 = take(size_t(m) * 4);
     L.front1 = take(size_t(m) * 4);
     L.front2 = take(size_t(m) * 4);
-    L.disc = take(size_t((m + 31) / 32) * 4 * 3);
     L.pmin = take(size_t(m) * 4);
-    L.bar = take(160 * 4);
+    L.bar = take(kPersistBarWords * 4);
     L.selector = take(size_t(kMlpParams + 2 * kMlpIn) * 4);
     // one-launch multiply: list samples, source prefix and per-chunk bucket offsets
     L.samples = take(size_t(kFMaxGrid) * kFSamples * 4);
@@ -262,13 +261,12 @@ struct spmspv_matrix {
     uint64_t* lb3 = nullptr;
     uint2* buckets = nullptr;
     uint32_t* visited = nullptr;
-    uint32_t* disc = nullptr;           // persistent BFS: three discovered-at-level bitmaps of m/32 words
-    int32_t* pmin = nullptr;            // persistent BFS: smallest frontier in-neighbour
+    int32_t* pmin = nullptr;            // connected components: the step's y values
     uint32_t* bar = nullptr;            // persistent BFS: grid barrier words
     int persist_grid = -1;              // co-resident workgroups of the persistent kernel (0 = unavailable)
     int fused_grid = -1;                // workgroups of the one-launch multiply (0 = unavailable)
     int32_t* front[2] = {nullptr, nullptr};
-    int32_t* front2 = nullptr;          // persistent BFS: third frontier list
+    int32_t* front2 = nullptr;          // connected components: the step's y indices
     int32_t maxdeg = 0;
     int device = 0;
     int num_cu = 256;
@@ -1068,7 +1066,6 @@ void bind_workspace(spmspv_matrix* A, int64_t m, int64_t n, int64_t nnz, const i
     A->front[0] = reinterpret_cast<int32_t*>(A->ws + L.front0);
     A->front[1] = reinterpret_cast<int32_t*>(A->ws + L.front1);
     A->front2 = reinterpret_cast<int32_t*>(A->ws + L.front2);
-    A->disc = reinterpret_cast<uint32_t*>(A->ws + L.disc);
     A->pmin = reinterpret_cast<int32_t*>(A->ws + L.pmin);
     A->bar = reinterpret_cast<uint32_t*>(A->ws + L.bar);
     A->selector = reinterpret_cast<float*>(A->ws + L.selector);
@@ -1084,15 +1081,14 @@ int read_ctrl(spmspv_matrix* A, Ctrl* h, hipStream_t s) {
     return SPMSPV_OK;
 }
 
-// Persistent BFS scratch between launches: bitmaps clear, pmin at INT32_MAX.
+// The fp64 cells of the HBM accumulator, which the persistent BFS borrows for
+// its per-vertex words: empty (-0.0) between calls.
 hipError_t reset_persistent_state(spmspv_matrix* A, hipStream_t s) {
-    hipError_t e = launch_fill_u32(A->disc, 0u, 3 * ((A->m + 31) / 32), s);
-    if (e == hipSuccess) e = launch_fill_u32(reinterpret_cast<uint32_t*>(A->pmin), 0x7fffffffu, A->m, s);
-    return e;
+    return launch_fill_u64(reinterpret_cast<uint64_t*>(A->ws + A->L.h_f64), 0x8000000000000000ull, A->L.h_rows, s);
 }
 
-// Clears the sticky error bits, and the persistent BFS scratch, which a
-// launch that gave up at a barrier leaves as it was.
+// Clears the sticky error bits, and the persistent BFS words, which a launch
+// that gave up at a barrier leaves as they were.
 int clear_err(spmspv_matrix* A, hipStream_t s) {
     HIP_TRY(launch_fill_u32(&A->ctrl->err, 0u, 1, s));
     HIP_TRY(reset_persistent_state(A, s));
@@ -1254,11 +1250,10 @@ int create_impl(spmspv_handle* h_out, int64_t m, int64_t n, int64_t nnz, int64_t
     if ((e = launch_exclusive_scan_i32(A->rcp, m + 1, reinterpret_cast<int32_t*>(A->ws + L.partials), s)) !=
         hipSuccess)
         return bail(hip_fail(e, "row count scan"));
-    if ((e = reset_persistent_state(A, s)) != hipSuccess || (e = launch_fill_u32(A->bar, 0u, 160, s)) != hipSuccess)
+    if ((e = launch_fill_u32(A->bar, 0u, kPersistBarWords, s)) != hipSuccess)
         return bail(hip_fail(e, "persistent BFS state"));
     // the HBM accumulator starts (and is left after every call) empty
-    if ((e = launch_fill_u64(reinterpret_cast<uint64_t*>(A->ws + L.h_f64), 0x8000000000000000ull, L.h_rows, s)) !=
-            hipSuccess ||
+    if ((e = reset_persistent_state(A, s)) != hipSuccess ||
         (e = launch_fill_u32(reinterpret_cast<uint32_t*>(A->ws + L.h_i32), 0x7fffffffu, L.h_rows, s)) != hipSuccess ||
         (e = launch_fill_u32(reinterpret_cast<uint32_t*>(A->ws + L.h_orbits), 0u, (L.h_rows + 31) / 32, s)) !=
             hipSuccess ||
@@ -1860,10 +1855,8 @@ int bfs_run(spmspv_handle A, int semiring, int32_t root, int flags, int32_t* lev
         pa.n = (int32_t)A->m;
         pa.front[0] = A->front[0];
         pa.front[1] = A->front[1];
-        pa.front[2] = A->front2;
         pa.visited = A->visited;
-        for (int k = 0; k < 3; ++k) pa.disc[k] = A->disc + k * ((A->m + 31) / 32);
-        pa.pmin = A->pmin;
+        pa.state = reinterpret_cast<uint64_t*>(A->ws + A->L.h_f64);
         pa.bar = A->bar;
     }
     if (learned_gate) {
@@ -1879,7 +1872,7 @@ int bfs_run(spmspv_handle A, int semiring, int32_t root, int flags, int32_t* lev
     for (int64_t batch = 0; h.f > 0; ++batch) {
         if (batch * kGraphLevels > A->n + kGraphLevels) return fail(SPMSPV_EDEVICE, "BFS did not terminate");
         if (persist) {
-            HIP_TRY(launch_fill_u32(A->bar, 0u, 160, s));   // arrivals, append counters, barrier count
+            HIP_TRY(launch_fill_u32(A->bar, 0u, kPersistBarWords, s));   // arrivals, append counters, barrier count
             HIP_TRY(launch_bfs_persistent(pa, semiring == SR_MIN_SELECT2ND, A->persist_grid, s));
             const int rc = read_ctrl(A, &h, s);
             if (rc) return rc;
@@ -2704,8 +2697,6 @@ int cc_run(spmspv_handle A, int flags, int32_t* labels, int32_t* h_iters, void* 
         HIP_TRY(hipMemcpyAsync(&hf, &A->ctrl->f, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
     }
-    // the persistent BFS expects its scratch (y values lived in it) reset
-    HIP_TRY(reset_persistent_state(A, s));
     Ctrl h{};
     int rc = read_ctrl(A, &h, s);
     if (rc) return rc;

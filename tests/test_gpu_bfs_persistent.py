@@ -110,3 +110,39 @@ def test_persistent_hand_off_from_every_slot(spv, tail):
     check(spv, M, A, root, 2, 0)
     check(spv, M, A, root, 1, spv.PERSISTENT | spv.USE_GRAPH)
     check(spv, M, A, int(synth.roots(A, 1, seed=tail)[0]), 2, spv.PERSISTENT)
+
+
+@pytest.mark.parametrize("fan", [(64, 8, 63, 1, 1), (64, 7, 9, 8, 1), (60, 8, 1, 60, 2), (64, 63, 15, 1, 1)])
+@pytest.mark.parametrize("semiring", [1, 2])
+def test_persistent_uneven_growth(spv, fan, semiring):
+    """One workgroup discovers a whole level: parts of the frontier that end
+    at its threads (512), outgrow them (a new deal), outgrow its list (4096)
+    and the persistent range (65536).  The last two levels join pairwise, so
+    parents are a minimum over two."""
+    sizes = [1]
+    for k in fan:
+        sizes.append(sizes[-1] * k)
+    sizes += [(sizes[-1] + 1) // 2, (sizes[-1] + 3) // 4]
+    first = np.concatenate([[0], np.cumsum(sizes)])
+    n = int(first[-1])
+    r, c = [], []
+    for lv, (a, b) in enumerate(zip(sizes[:-1], sizes[1:])):
+        if b >= a:
+            child = np.arange(b)
+            r.append(first[lv + 1] + child)
+            c.append(first[lv] + child // (b // a))
+        else:
+            up = np.arange(a)
+            r.append(first[lv + 1] + up // 2)
+            c.append(first[lv] + up)
+    rng = np.random.default_rng(len(fan) + semiring)
+    name = rng.permutation(n).astype(np.int32)
+    r, c = name[np.concatenate(r)], name[np.concatenate(c)]
+    colptr, rowids = synth.coo_to_csc(n, n, np.concatenate([r, c]), np.concatenate([c, r]))
+    A = synth.CSC(n, n, colptr, rowids, None, "fan")
+    assert int(np.diff(A.colptr).max()) <= 64
+    M = spv.Matrix.from_csc(A, pattern=True)
+    for _ in range(2):
+        check(spv, M, A, int(name[0]), semiring, spv.PERSISTENT)
+        check(spv, M, A, int(name[n - 1]), semiring, spv.PERSISTENT)
+    M.close()
