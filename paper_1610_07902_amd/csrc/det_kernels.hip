@@ -408,6 +408,7 @@ __global__ __launch_bounds__(kFoldBlock) void k_det_fold(DetArgs a, const uint2*
         const int64_t total = a.counts[nt];
         __hip_atomic_store(&a.ctrl->nnz_y, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (a.d_nnz_y) *a.d_nnz_y = total;
+        report_nnz(a.rep, a.ctrl, total);
     }
     for (int t = blockIdx.x; t < nt; t += gridDim.x) {
         const int64_t base = (int64_t)t * kDetTile;
@@ -532,7 +533,7 @@ __global__ __launch_bounds__(kFoldBlock) void k_det_fold(DetArgs a, const uint2*
                 if (slot < kDetLongPerBlock)
                     s_long[slot] = make_int4((int)e0.x, (int)__float_as_uint(acc), (int)(base + last + 1), (int)p);
                 else
-                    atomicOr(&a.ctrl->err, ERR_SPIN);   // not reached (see above)
+                    raise_err(&a.ctrl->err, ERR_SPIN, a.rep);   // not reached (see above)
             } else if (p < a.y_cap) {
                 a.y_idx[p] = (int32_t)e0.x;
                 if (a.y_val) a.y_val[p] = acc;

@@ -36,6 +36,21 @@ __device__ __forceinline__ void st_ctrl_u(uint32_t* p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A waiting call's results to the host (system scope: pinned memory), by one
+// thread of the call's last kernel; an error bit that this kernel itself
+// raises is reported by raise_err, wherever it happens.
+__device__ __forceinline__ void report_nnz(Report* rep, const Ctrl* ctrl, int64_t nnz) {
+    if (!rep) return;
+    const uint32_t err = __hip_atomic_load(&ctrl->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&rep->nnz, nnz, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&rep->err, err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&rep->state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void raise_err(uint32_t* err, uint32_t bits, Report* rep) {
+    atomicOr(err, bits);
+    if (rep) __hip_atomic_store(&rep->bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
@@ -47,7 +62,7 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
 // `tile`, returns the exclusive prefix and publishes the inclusive one.
 // A wait that exceeds kSpinMax polls sets ERR_SPIN and returns a partial
 // prefix rather than hanging.
-__device__ inline uint64_t lookback(uint64_t* st, int tile, uint64_t agg, uint32_t* err) {
+__device__ inline uint64_t lookback(uint64_t* st, int tile, uint64_t agg, uint32_t* err, Report* rep = nullptr) {
     const int lane = threadIdx.x & (kWave - 1);
     if (tile == 0) {
         if (lane == 0) st_release64(&st[0], LB_INC | (agg & LB_VAL));
@@ -66,7 +81,7 @@ __device__ inline uint64_t lookback(uint64_t* st, int tile, uint64_t agg, uint32
         const uint64_t need = inc_mask ? (((inc_mask & (~inc_mask + 1)) << 1) - 1) : ~0ull;
         if (empty_mask & need) {
             if (++spins > kSpinMax) {
-                if (lane == 0) atomicOr(err, ERR_SPIN);
+                if (lane == 0) raise_err(err, ERR_SPIN, rep);
                 break;
             }
             __builtin_amdgcn_s_sleep(1);

@@ -131,11 +131,12 @@ __global__ __launch_bounds__(kCBlock) void k_combine(CombineArgs a) {
         if (blockIdx.x == 0 && tid == 0) {
             __hip_atomic_store(&a.ctrl->nnz_y, (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (a.d_nnz_y) *a.d_nnz_y = 0;
+            report_nnz(a.rep, a.ctrl, 0);
         }
         return;
     }
     if (ntiles > a.lb_n) {   // more tiles than look-back words: not reached (sized for t and w at their largest)
-        if (blockIdx.x == 0 && tid == 0) atomicOr(&a.ctrl->err, ERR_SPIN);
+        if (blockIdx.x == 0 && tid == 0) raise_err(&a.ctrl->err, ERR_SPIN, a.rep);
         return;
     }
     bool disorder = false;
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(kCBlock) void k_combine(CombineArgs a) {
         int tile_total;
         const int pre = block_exclusive_i32<kCBlock>(cnt, s_tmp, tile_total);
         if (tid < kWave) {
-            const uint64_t e = lookback(a.lb, (int)tile, (uint64_t)tile_total, &a.ctrl->err);
+            const uint64_t e = lookback(a.lb, (int)tile, (uint64_t)tile_total, &a.ctrl->err, a.rep);
             if (tid == 0) s_excl = (int64_t)e;
         }
         __syncthreads();
@@ -243,10 +244,11 @@ __global__ __launch_bounds__(kCBlock) void k_combine(CombineArgs a) {
             const int64_t out = s_excl + pre + cnt;
             __hip_atomic_store(&a.ctrl->nnz_y, out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (a.d_nnz_y) *a.d_nnz_y = out;
+            report_nnz(a.rep, a.ctrl, out);
         }
         __syncthreads();
     }
-    if (disorder) atomicOr(&a.ctrl->err, ERR_ORDER);
+    if (disorder) raise_err(&a.ctrl->err, ERR_ORDER, a.rep);
 }
 
 }  // namespace

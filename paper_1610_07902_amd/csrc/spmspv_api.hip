@@ -231,6 +231,70 @@ BatchLayout make_batch_layout(int64_t m, int64_t n, int64_t nnz, int max_batch, 
     return L;
 }
 
+// Pinned host memory for what calls read back: one slot per handle, from slabs
+// shared by the process (pinning takes about 0.1 ms, as long as the rest of
+// a small create).  A slab other than the first goes back once all of its
+// slots are free.  The pool outlives the handles (it is never destroyed: a
+// handle may be closed while the process exits).
+struct alignas(512) PinSlot {
+    Ctrl ctrl;
+    Report rep;
+    uint64_t word;
+};
+static_assert(sizeof(PinSlot) == 512, "two slots never share a cache line");
+
+class PinPool {
+   public:
+    PinSlot* take() {
+        std::lock_guard<std::mutex> g(mu_);
+        for (auto& sl : slabs_)
+            if (!sl.free.empty()) return pop(sl);
+        void* p = nullptr;
+        if (hipHostMalloc(&p, kSlots * sizeof(PinSlot), hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;   // the caller copies through pageable memory
+        }
+        Slab sl;
+        sl.base = static_cast<PinSlot*>(p);
+        for (int k = kSlots; k-- > 0;) sl.free.push_back(sl.base + k);
+        slabs_.push_back(std::move(sl));
+        return pop(slabs_.back());
+    }
+    void give(PinSlot* s) {
+        if (!s) return;
+        std::lock_guard<std::mutex> g(mu_);
+        for (size_t k = 0; k < slabs_.size(); ++k) {
+            Slab& sl = slabs_[k];
+            if (s < sl.base || s >= sl.base + kSlots) continue;
+            sl.free.push_back(s);
+            if (k > 0 && sl.free.size() == (size_t)kSlots) {
+                (void)hipHostFree(sl.base);
+                slabs_.erase(slabs_.begin() + (std::ptrdiff_t)k);
+            }
+            return;
+        }
+    }
+
+   private:
+    static constexpr int kSlots = 128;
+    struct Slab {
+        PinSlot* base = nullptr;
+        std::vector<PinSlot*> free;
+    };
+    static PinSlot* pop(Slab& sl) {
+        PinSlot* s = sl.free.back();
+        sl.free.pop_back();
+        return s;
+    }
+    std::mutex mu_;
+    std::vector<Slab> slabs_;
+};
+
+PinPool& pin_pool() {
+    static PinPool* pool = new PinPool;
+    return *pool;
+}
+
 struct BatchCtx {
     bool bound = false;
     bool bfs = false;
@@ -316,6 +380,8 @@ struct spmspv_matrix {
     int32_t* bv_idx = nullptr;
     uint32_t* bv_val = nullptr;
     int32_t* bv_tiles = nullptr;
+    PinSlot* pin = nullptr;             // read-back slot (nullptr: copies go through pageable memory)
+    ~spmspv_matrix() { pin_pool().give(pin); }
 };
 
 namespace {
@@ -413,7 +479,7 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
             const void* x_val, int32_t* y_idx, void* y_val, int64_t y_cap, int64_t* d_nnz_y, bool bfs,
             const uint32_t* mask, hipStream_t s, hipEvent_t* ev, bool diropt = false, int tile_log2 = -1,
             int phases = 3, int clear_nb = 0, bool learned_gate = false, int mask_keep = 0, bool left = false,
-            int variant = -1, uint32_t* y_bits = nullptr) {
+            int variant = -1, uint32_t* y_bits = nullptr, Report* rep = nullptr) {
     // The operand: A, or for left multiplication A^T through the CSR copy
     // (y' = x'A is y = A^T x; Background, Notation).  The CSR copy's row
     // pointer is A^T's column pointer and A's column pointer is A^T's
@@ -547,6 +613,7 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
     ma.h_touched = reinterpret_cast<uint32_t*>(A->ws + A->L.h_touched);
     ma.h_split = std::max(1, std::min(1024, 4 * A->num_cu / nb));   // about four workgroups per CU
     ma.y_bits = bfs ? nullptr : y_bits;
+    ma.rep = rep;
 
     // With profiling, each kernel's own start and end timestamps go to a pair
     // of events (scan, scatter, merge).
@@ -578,7 +645,7 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
 // (det_kernels.hip).  y is ascending.
 int enqueue_det(spmspv_matrix* A, int xmode, int64_t f, const int32_t* x_idx, const void* x_val, int32_t* y_idx,
                 float* y_val, int64_t y_cap, int64_t* d_nnz_y, const uint32_t* mask, int mask_keep, bool left,
-                hipStream_t s) {
+                hipStream_t s, Report* rep) {
     const Layout& L = A->L;
     if (!L.det)
         return fail(SPMSPV_EUNSUPPORTED, "SPMSPV_DETERMINISTIC needs a handle whose workspace was sized and "
@@ -627,6 +694,7 @@ int enqueue_det(spmspv_matrix* A, int xmode, int64_t f, const int32_t* x_idx, co
     d.y_val = y_val;
     d.y_cap = y_cap;
     d.d_nnz_y = d_nnz_y;
+    d.rep = rep;
     int32_t* partials = reinterpret_cast<int32_t*>(A->ws + L.det_partials);
     uint2* cur = A->buckets;
     uint2* other = reinterpret_cast<uint2*>(A->ws + L.det_list);
@@ -862,7 +930,7 @@ int batch_shape(const spmspv_matrix* A, int nbatch, int semiring, spmspv_schedul
 
 int enqueue_batch(spmspv_matrix* A, int semiring, int xmode, int nbatch, const int64_t* x_off, const int32_t* x_idx,
                   const void* x_val, int64_t* y_off, int32_t* y_idx, void* y_val, int64_t y_cap, bool bfs,
-                  hipStream_t s) {
+                  hipStream_t s, Report* rep = nullptr) {
     BatchCtx& B = A->batch;
     char* w = B.ws;
     const BatchLayout& L = B.L;
@@ -964,6 +1032,7 @@ int enqueue_batch(spmspv_matrix* A, int semiring, int xmode, int nbatch, const i
     ma.yoff = y_off;
     ma.n_stride = A->n;
     ma.mask_words = L.mask_words;
+    ma.rep = rep;
 
     // With distinct indices inside each vector (a precondition of every
     // multiply; multi-source BFS frontiers are sets), vector x puts at most
@@ -1076,8 +1145,49 @@ void bind_workspace(spmspv_matrix* A, int64_t m, int64_t n, int64_t nnz, const i
 }
 
 int read_ctrl(spmspv_matrix* A, Ctrl* h, hipStream_t s) {
-    HIP_TRY(hipMemcpyAsync(h, A->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
+    Ctrl* to = A->pin ? &A->pin->ctrl : h;
+    HIP_TRY(hipMemcpyAsync(to, A->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    if (to != h) *h = *to;
+    return SPMSPV_OK;
+}
+
+// One 64-bit device word (and, with h, the control block) to the host.
+int read_word(spmspv_matrix* A, const void* dev, uint64_t* out, Ctrl* h, hipStream_t s) {
+    HIP_TRY(hipMemcpyAsync(A->pin ? &A->pin->word : out, dev, 8, hipMemcpyDeviceToHost, s));
+    if (h) {
+        if (const int rc = read_ctrl(A, h, s)) return rc;
+    } else {
+        HIP_TRY(hipStreamSynchronize(s));
+    }
+    if (A->pin) *out = A->pin->word;
+    return SPMSPV_OK;
+}
+
+// A call that waits passes the report of its handle's slot (cleared here,
+// before the call's kernels) to its last kernel; finish_call waits for the
+// stream and returns nnz(y) and the error bits, from the report or, where
+// the kernels wrote none or raised an error themselves, from the control
+// block.
+Report* begin_report(spmspv_matrix* A, const int64_t* h_nnz) {
+    if (!h_nnz || !A->pin) return nullptr;
+    A->pin->rep = Report{};
+    return &A->pin->rep;
+}
+
+int finish_call(spmspv_matrix* A, Report* rep, hipStream_t s, int64_t* nnz, uint32_t* err) {
+    if (rep) {
+        HIP_TRY(hipStreamSynchronize(s));
+        if (__atomic_load_n(&rep->state, __ATOMIC_ACQUIRE) == 1u && __atomic_load_n(&rep->bad, __ATOMIC_RELAXED) == 0u) {
+            *nnz = __atomic_load_n(&rep->nnz, __ATOMIC_RELAXED);
+            *err = __atomic_load_n(&rep->err, __ATOMIC_RELAXED);
+            return SPMSPV_OK;
+        }
+    }
+    Ctrl h{};
+    if (const int rc = read_ctrl(A, &h, s)) return rc;
+    *nnz = h.nnz_y;
+    *err = h.err;
     return SPMSPV_OK;
 }
 
@@ -1230,6 +1340,8 @@ int create_impl(spmspv_handle* h_out, int64_t m, int64_t n, int64_t nnz, int64_t
         A->num_cu = v;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, A->device) == hipSuccess && v > 0)
         A->lds_max = (size_t)v;
+
+    A->pin = pin_pool().take();
 
     // Zero the control block and the per-call look-back / counter state.
     const size_t zero_end = L.buckets;
@@ -1432,6 +1544,7 @@ int spmspv_run_masked(spmspv_handle A, int semiring, int flags, int64_t f, const
         }
     }
     hipEvent_t* ev = (flags & SPMSPV_PROFILE) ? profile_slot(A) : nullptr;
+    Report* const rep = begin_report(A, h_nnz_y);
     int rc;
     if ((flags & SPMSPV_DETERMINISTIC) && semiring == SR_PLUS_TIMES) {
         // min and or are order-free: only plus-times takes the ordered fold
@@ -1440,13 +1553,13 @@ int spmspv_run_masked(spmspv_handle A, int semiring, int flags, int64_t f, const
         const spmspv_schedule keep = A->sched;
         if (A->sched_default && !left) A->sched = sized_for_call(A, f);
         rc = enqueue_det(A, xmode, f, x_idx, x_val, y_idx, static_cast<float*>(y_val), y_capacity, d_nnz_y, mask, 0,
-                         left, s);
+                         left, s, rep);
         A->sched = keep;
     } else if (left) {
         const spmspv_schedule keep = A->sched;
         A->sched.direction = 0;
         rc = enqueue(A, semiring, xmode, f, nullptr, x_idx, x_val, y_idx, y_val, y_capacity, d_nnz_y, false, mask, s,
-                     ev, false, -1, 3, 0, false, 0, true);
+                     ev, false, -1, 3, 0, false, 0, true, -1, nullptr, rep);
         A->sched = keep;
     } else if (flags & SPMSPV_USE_SELECTOR) {
         if (!A->selector_loaded) return fail(SPMSPV_EINVAL, "no selector weights loaded");
@@ -1476,21 +1589,20 @@ int spmspv_run_masked(spmspv_handle A, int semiring, int flags, int64_t f, const
                                fnb, s, ev);
         else
             rc = enqueue(A, semiring, xmode, f, nullptr, x_idx, x_val, y_idx, y_val, y_capacity, d_nnz_y, false, mask,
-                         s, ev);
+                         s, ev, false, -1, 3, 0, false, 0, false, -1, nullptr, rep);
         A->sched = keep;
     }
     if (rc) return rc;
     if (h_nnz_y) {
-        Ctrl h{};
-        rc = read_ctrl(A, &h, s);
+        uint32_t err = 0;
+        rc = finish_call(A, rep, s, h_nnz_y, &err);
         if (rc) return rc;
-        *h_nnz_y = h.nnz_y;
-        if (h.err) {
+        if (err) {
             clear_err(A, s);
-            return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(h.err) +
+            return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(err) +
                                             " (1 = x index range, 2 = duplicate x index, 4 = look-back bound)");
         }
-        if (h.nnz_y > y_capacity) return fail(SPMSPV_ECAPACITY, "nnz(y) exceeds y_capacity");
+        if (*h_nnz_y > y_capacity) return fail(SPMSPV_ECAPACITY, "nnz(y) exceeds y_capacity");
     }
     return SPMSPV_OK;
 }
@@ -1522,22 +1634,22 @@ int spmspv_run_bitvector(spmspv_handle A, int semiring, int flags, const uint32_
     // list goes to x's storage (the scan has copied what it needs from x
     // before the merge writes y)
     const spmspv_schedule keep = A->sched;
+    Report* const rep = begin_report(A, h_nnz_y);
     A->sched.direction = 0;
     const int rc = enqueue(A, semiring, xmode, 0, &A->ctrl->bv_f, A->bv_idx, x_val, A->bv_idx, y_val, y_cap, d_nnz_y,
-                           false, nullptr, s, nullptr, false, -1, 3, 0, false, 0, left, -1, y_bits);
+                           false, nullptr, s, nullptr, false, -1, 3, 0, false, 0, left, -1, y_bits, rep);
     A->sched = keep;
     if (rc) return rc;
     if (h_nnz_y) {
-        Ctrl h{};
-        const int r = read_ctrl(A, &h, s);
+        uint32_t err = 0;
+        const int r = finish_call(A, rep, s, h_nnz_y, &err);
         if (r) return r;
-        *h_nnz_y = h.nnz_y;
-        if (h.err) {
+        if (err) {
             clear_err(A, s);
-            return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(h.err) +
+            return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(err) +
                                             " (1 = x bit set past the vector length)");
         }
-        if (h.nnz_y > y_capacity) return fail(SPMSPV_ECAPACITY, "nnz(y) exceeds y_capacity");
+        if (*h_nnz_y > y_capacity) return fail(SPMSPV_ECAPACITY, "nnz(y) exceeds y_capacity");
     }
     return SPMSPV_OK;
 }
@@ -1616,6 +1728,8 @@ int spmspv_run_graphblas(spmspv_handle A, int semiring, int flags, int64_t f, co
     void* t_val = direct ? y_val : static_cast<void*>(A->bv_val);
     const int64_t t_cap = direct ? y_capacity : ylen;
     int64_t* t_count = direct ? d_nnz_y : &A->ctrl->aux_count;
+    Report* const rep = begin_report(A, h_nnz_y);
+    Report* const t_rep = direct ? rep : nullptr;
     const spmspv_schedule keep = A->sched;
     if (A->sched_default && !left) A->sched = sized_for_call(A, f);
     A->sched.direction = 0;
@@ -1623,10 +1737,10 @@ int spmspv_run_graphblas(spmspv_handle A, int semiring, int flags, int64_t f, co
     if (!has_mask && complement) {
         // no row is in the mask: t is empty
         rc = enqueue(A, semiring, xmode, 0, nullptr, x_idx, x_val, t_idx, t_val, t_cap, t_count, false, nullptr, s,
-                     nullptr, false, -1, 3, 0, false, 0, left);
+                     nullptr, false, -1, 3, 0, false, 0, left, -1, nullptr, t_rep);
     } else {
         rc = enqueue(A, semiring, xmode, f, nullptr, x_idx, x_val, t_idx, t_val, t_cap, t_count, false, bits, s,
-                     nullptr, false, -1, 3, 0, false, complement ? 0 : 1, left);
+                     nullptr, false, -1, 3, 0, false, complement ? 0 : 1, left, -1, nullptr, t_rep);
     }
     A->sched = keep;
     if (rc) return rc;
@@ -1650,6 +1764,7 @@ int spmspv_run_graphblas(spmspv_handle A, int semiring, int flags, int64_t f, co
         ca.ctrl = A->ctrl;
         ca.lb = reinterpret_cast<uint64_t*>(A->ws + A->L.gb_lb);
         ca.lb_n = (int32_t)gb_lb_words(ylen);
+        ca.rep = rep;
         HIP_TRY(launch_clear_u64(ca.lb, ca.lb_n, s));
         int64_t grid = (ylen + w_count + kCombineTile - 1) / kCombineTile;
         if (grid < 1) grid = 1;
@@ -1659,17 +1774,16 @@ int spmspv_run_graphblas(spmspv_handle A, int semiring, int flags, int64_t f, co
         HIP_TRY(launch_combine(ca, semiring, (int)grid, s));
     }
     if (h_nnz_y) {
-        Ctrl h{};
-        rc = read_ctrl(A, &h, s);
+        uint32_t err = 0;
+        rc = finish_call(A, rep, s, h_nnz_y, &err);
         if (rc) return rc;
-        *h_nnz_y = h.nnz_y;
-        if (h.err) {
+        if (err) {
             clear_err(A, s);
-            return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(h.err) +
+            return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(err) +
                                             " (1 = x index range, 2 = duplicate x index, 4 = look-back bound, "
                                             "32 = mask or w index range, 64 = w not ascending)");
         }
-        if (h.nnz_y > y_capacity) return fail(SPMSPV_ECAPACITY, "nnz(y) exceeds y_capacity");
+        if (*h_nnz_y > y_capacity) return fail(SPMSPV_ECAPACITY, "nnz(y) exceeds y_capacity");
     }
     return SPMSPV_OK;
 }
@@ -2043,20 +2157,21 @@ int spmspv_get_batch_schedule(spmspv_handle A, int semiring, int nbatch, spmspv_
 }
 
 namespace {
-int batch_status(spmspv_matrix* A, hipStream_t s, int64_t* total) {
-    Ctrl h{};
-    int rc = read_ctrl(A, &h, s);
+int batch_status(spmspv_matrix* A, Report* rep, hipStream_t s, int64_t* total) {
+    int64_t nnz = 0;
+    uint32_t err = 0;
+    const int rc = finish_call(A, rep, s, &nnz, &err);
     if (rc) return rc;
-    if (h.err) {
+    if (err) {
         clear_err(A, s);
-        if (h.err & ERR_X_RANGE) return fail(SPMSPV_EINVAL, "x index or vector offset out of range");
-        if ((h.err & ERR_BUCKET_OVERFLOW) && A->batch.fixed_last)
+        if (err & ERR_X_RANGE) return fail(SPMSPV_EINVAL, "x index or vector offset out of range");
+        if ((err & ERR_BUCKET_OVERFLOW) && A->batch.fixed_last)
             return fail(SPMSPV_EDEVICE, "a bucket slice overflowed: repeated x index within a vector");
-        if (h.err & ERR_BUCKET_OVERFLOW)
+        if (err & ERR_BUCKET_OVERFLOW)
             return fail(SPMSPV_ECAPACITY, "products exceed the batch workspace's max_products");
-        return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(h.err));
+        return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(err));
     }
-    if (total) *total = h.nnz_y;
+    if (total) *total = nnz;
     return SPMSPV_OK;
 }
 }  // namespace
@@ -2097,12 +2212,13 @@ int spmspv_run_batch(spmspv_handle A, int semiring, int flags, int nbatch, const
                 stamp[(size_t)j] = b;
             }
     }
+    Report* const rep = begin_report(A, h_nnz_total);
     const int rc = enqueue_batch(A, semiring, xmode, nbatch, x_off, x_idx, x_val, y_off, y_idx, y_val, y_capacity,
-                                 false, s);
+                                 false, s, rep);
     if (rc) return rc;
     if (h_nnz_total) {
         int64_t total = 0;
-        const int st = batch_status(A, s, &total);
+        const int st = batch_status(A, rep, s, &total);
         if (st) return st;
         *h_nnz_total = total;
         if (total > y_capacity)
@@ -2143,14 +2259,14 @@ int msbfs_diropt(spmspv_matrix* A, int semiring, int nsrc, int32_t* level, int32
     int32_t hf = nsrc;
     int64_t lv = 0;   // the current frontier's position in the level sequence
     bool pull = false;
+    Ctrl h{};
     for (;;) {
         if (lv > A->n + 1) return fail(SPMSPV_EDEVICE, "BFS did not terminate");
         HIP_TRY(launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 0ull, 1, s));
         HIP_TRY(launch_ms_degsum(front[lv & 1], xoff[lv & 1], nsrc, A->colptr, (int32_t)A->n, counter, s));
-        unsigned long long mf = 0;
-        HIP_TRY(hipMemcpyAsync(&mf, counter, sizeof(mf), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(&hf, &A->ctrl->f, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        uint64_t mf = 0;
+        if (const int rc = read_word(A, counter, &mf, &h, s)) return rc;
+        hf = h.f;
         if (hf <= 0) break;
         m_u -= (double)mf;
         if ((double)mf * alpha > m_u) {
@@ -2162,10 +2278,7 @@ int msbfs_diropt(spmspv_matrix* A, int semiring, int nsrc, int32_t* level, int32
         if (rc) return rc;
         ++lv;
     }
-    Ctrl h{};
-    int rc = read_ctrl(A, &h, s);
-    if (rc) return rc;
-    int32_t levels = h.level;
+    int32_t levels = h.level;   // as read after the last push level
     if (pull && hf > 0) {
         // level of the current frontier: the scans have counted the push levels
         int32_t cur = h.level;
@@ -2194,9 +2307,8 @@ int msbfs_diropt(spmspv_matrix* A, int semiring, int nsrc, int32_t* level, int32
             ma.lvl = cur + 1;
             HIP_TRY(launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 0ull, 1, s));
             HIP_TRY(launch_ms_pull(ma, ma.parent != nullptr, A->num_cu, s));
-            unsigned long long found = 0;
-            HIP_TRY(hipMemcpyAsync(&found, counter, sizeof(found), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
+            uint64_t found = 0;
+            if (const int rc = read_word(A, counter, &found, nullptr, s)) return rc;
             ++cur;   // the frontier was not empty
             if (found == 0) break;
             cf ^= 1;
@@ -2245,8 +2357,9 @@ int msbfs_run(spmspv_handle A, int semiring, int nsrc, const int32_t* h_roots, i
         return msbfs_diropt(A, semiring, nsrc, level, parent, h_num_levels, s);
     // Levels are enqueued kGraphLevels at a time; levels after the frontiers
     // empty are no-ops.  One host check of the total frontier per batch.
-    int32_t hf = nsrc;
-    for (int64_t l = 0; hf > 0; l += kGraphLevels) {
+    Ctrl h{};
+    h.f = nsrc;
+    for (int64_t l = 0; h.f > 0; l += kGraphLevels) {
         if (l > A->n + kGraphLevels) return fail(SPMSPV_EDEVICE, "BFS did not terminate");
         for (int k = 0; k < kGraphLevels; ++k) {
             const int64_t lv = l + k;
@@ -2254,12 +2367,9 @@ int msbfs_run(spmspv_handle A, int semiring, int nsrc, const int32_t* h_roots, i
                                front[(lv + 1) & 1], nullptr, L.max_f, true, s);
             if (rc) return rc;
         }
-        HIP_TRY(hipMemcpyAsync(&hf, &A->ctrl->f, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        rc = read_ctrl(A, &h, s);
+        if (rc) return rc;
     }
-    Ctrl h{};
-    rc = read_ctrl(A, &h, s);
-    if (rc) return rc;
     if (h.err) {
         clear_err(A, s);
         if (h.err & ERR_BUCKET_OVERFLOW)
@@ -2619,9 +2729,10 @@ int pagerank_run(spmspv_handle A, float damping, float tol, int max_iter, int fl
     HIP_TRY(launch_pr_init((int32_t)n, A->colptr, damping, rank, x_idx, x_val, A->ctrl, s));
     HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(&A->ctrl->bfs_mode), 0u, 1, s));
     A->level_classes.clear();
-    int32_t hf = 1;
+    Ctrl h{};
+    h.f = 1;
     int done = 0;
-    while (hf > 0 && done < max_iter) {
+    while (h.f > 0 && done < max_iter) {
         // kGraphLevels steps per host check; steps after x empties are no-ops
         // With the selector: one host read per multiply (bucket count and
         // direction), or with SPMSPV_USE_GRAPH the network's direction taken
@@ -2655,12 +2766,11 @@ int pagerank_run(spmspv_handle A, float damping, float tol, int max_iter, int fl
                                      s));
         }
         done += steps;
-        HIP_TRY(hipMemcpyAsync(&hf, &A->ctrl->f, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        if (const int rc = read_ctrl(A, &h, s)) return rc;
     }
-    Ctrl h{};
-    int rc = read_ctrl(A, &h, s);
-    if (rc) return rc;
+    if (done == 0) {   // max_iter == 0: nothing was read yet
+        if (const int rc = read_ctrl(A, &h, s)) return rc;
+    }
     if (h.err) {
         clear_err(A, s);
         return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(h.err));
@@ -2683,9 +2793,10 @@ int cc_run(spmspv_handle A, int flags, int32_t* labels, int32_t* h_iters, void* 
     int32_t* y_idx = A->front2;
     int32_t* y_val = A->pmin;
     HIP_TRY(launch_cc_init((int32_t)n, A->colptr, labels, x_idx, x_val, A->ctrl, s));
-    int32_t hf = 1;
+    Ctrl h{};
+    h.f = 1;
     int64_t done = 0;
-    while (hf > 0 && done <= n) {
+    while (h.f > 0 && done <= n) {
         // kGraphLevels steps per host check; steps after x empties are no-ops
         for (int k = 0; k < kGraphLevels; ++k) {
             const int rc = enqueue(A, SR_MIN_SELECT2ND, XV_BITS32, 0, &A->ctrl->f, x_idx, x_val, y_idx, y_val, n,
@@ -2694,17 +2805,13 @@ int cc_run(spmspv_handle A, int flags, int32_t* labels, int32_t* h_iters, void* 
             HIP_TRY(launch_cc_update((int32_t)n, A->colptr, labels, y_idx, y_val, x_idx, x_val, A->ctrl, s));
         }
         done += kGraphLevels;
-        HIP_TRY(hipMemcpyAsync(&hf, &A->ctrl->f, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        if (const int rc = read_ctrl(A, &h, s)) return rc;
     }
-    Ctrl h{};
-    int rc = read_ctrl(A, &h, s);
-    if (rc) return rc;
     if (h.err) {
         clear_err(A, s);
         return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(h.err));
     }
-    if (hf > 0) return fail(SPMSPV_EDEVICE, "labels still changing after n steps");
+    if (h.f > 0) return fail(SPMSPV_EDEVICE, "labels still changing after n steps");
     if (h_iters) *h_iters = h.level;
     return SPMSPV_OK;
 }

@@ -633,6 +633,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
             if (b == a.nb - 1) {
                 a.ctrl->nnz_y = 0;
                 if (a.d_nnz_y) *a.d_nnz_y = 0;
+                report_nnz(a.rep, a.ctrl, 0);
                 if (a.set_f) st_ctrl(&a.ctrl->f, 0);
                 if (BATCH) a.yoff[a.nbatch] = 0;
             }
@@ -711,7 +712,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
             add_rows<SR, kBatch>(r, v, ok, spa, bm, sparse);
         }
     }
-    if (bad) atomicOr(&a.ctrl->err, ERR_BUCKET_OVERFLOW);
+    if (bad) raise_err(&a.ctrl->err, ERR_BUCKET_OVERFLOW, a.rep);
     __syncthreads();
     if (kWide && !sparse) {
         touched_bits64<BLOCK>(spa, bm, rows);
@@ -722,7 +723,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
     int ucnt;
     (void)block_exclusive_i32<BLOCK>(pc, s_tmp, ucnt);
     if (tid < kWave) {
-        const uint64_t e = lookback(a.lb3, b, (uint64_t)ucnt, &a.ctrl->err);
+        const uint64_t e = lookback(a.lb3, b, (uint64_t)ucnt, &a.ctrl->err, a.rep);
         if (tid == 0) {
             s_excl = (int64_t)e;
             if (BATCH && bt == 0) a.yoff[xb] = (int64_t)e;
@@ -730,6 +731,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
                 const int64_t total = (int64_t)e + ucnt;
                 a.ctrl->nnz_y = total;
                 if (a.d_nnz_y) *a.d_nnz_y = total;
+                report_nnz(a.rep, a.ctrl, total);
                 if (a.set_f) st_ctrl(&a.ctrl->f, (int32_t)total);
                 if (BATCH) a.yoff[a.nbatch] = total;
             }
