@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["spmspv_api.hip", "spmspv_kernels.hip", "setup_kernels.hip", "pull_kernels.hip", "mlp_kernels.hip",
+SOURCES = ["spmspv_api.hip", "spmspv_kernels.hip", "expand_kernels.hip", "setup_kernels.hip", "pull_kernels.hip", "mlp_kernels.hip",
            "pagerank_kernels.hip", "bfs_persistent.hip", "fused_kernels.hip",
            "graphblas_kernels.hip", "cc_kernels.hip", "format_kernels.hip", "det_kernels.hip",
            "hbm_merge_kernels.hip", "msbfs_kernels.hip"]

@@ -49,7 +49,7 @@ __device__ __forceinline__ int det_group(int nt) {
 // per compute unit where the chunk's table fits twice in LDS (4096-product
 // chunks); at 66 registers only one fitted.
 __global__ __launch_bounds__(kGatherBlock, 8) void k_det_gather(DetArgs a, uint2* list) {
-    extern __shared__ int32_t s_off[];   // the chunk's column table, 3 x (chunk + 2) words
+    extern __shared__ __align__(16) int32_t s_off[];   // the chunk's column table, 3 x (chunk + 2) words
     // every word the first chunk's set-up needs, loaded together (the grid is
     // at most the workspace's chunk count, so chunk_col has both entries; they
     // are used only if the chunks exist)

@@ -122,16 +122,34 @@ __device__ __forceinline__ uint64_t block_exclusive_u64(uint64_t v, uint64_t* s_
     return pre + x - v;
 }
 
+// Inclusive sum over the wave's lanes with data-parallel moves (shifts within
+// rows of 16 lanes, then the rows' last lanes broadcast): register moves
+// where __shfl_up goes through LDS six times in a row.
+__device__ __forceinline__ int wave_inclusive_i32(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// Every load of the array is issued before this point and every use comes
+// after it: neither a later condition nor the register allocator's ordering
+// turns the loads into a chain of single round trips.
+template <typename T, int K>
+__device__ __forceinline__ void loaded(T (&v)[K]) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < K; ++i) asm volatile("" : "+v"(v[i]));
+}
+
 template <int BLOCK>
 __device__ __forceinline__ int block_exclusive_i32(int v, int* s_tmp, int& total) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = threadIdx.x / kWave;
-    int x = v;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int y = __shfl_up(x, d, kWave);
-        if (lane >= d) x += y;
-    }
+    const int x = wave_inclusive_i32(v);
     if (lane == kWave - 1) s_tmp[wid] = x;
     __syncthreads();
     // every lane reads the wave totals (broadcast reads, independent of
@@ -148,12 +166,58 @@ __device__ __forceinline__ int block_exclusive_i32(int v, int* s_tmp, int& total
     return pre + x - v;
 }
 
+// The call's statistics from the expansion phase's per-workgroup sums, by one
+// workgroup of the merge.
+template <int BLOCK>
+__device__ __forceinline__ void collect_stats(const MergeArgs& a) {
+    __shared__ int64_t s_w[BLOCK / kWave];
+    __shared__ int32_t s_c[BLOCK / kWave], s_l[BLOCK / kWave];
+    int64_t w = 0;
+    int32_t c = 0, l = 0;
+    for (int i = threadIdx.x; i < a.stat_n; i += BLOCK) {
+        const ExpandStat st = a.stat[i];
+        w += st.products;
+        c += st.columns;
+        l = max(l, st.longest);
+    }
+#pragma unroll
+    for (int d = kWave / 2; d >= 1; d >>= 1) {
+        w += __shfl_xor(w, d, kWave);
+        c += __shfl_xor(c, d, kWave);
+        l = max(l, __shfl_xor(l, d, kWave));
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        s_w[threadIdx.x / kWave] = w;
+        s_c[threadIdx.x / kWave] = c;
+        s_l[threadIdx.x / kWave] = l;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < BLOCK / kWave; ++k) {
+        w += s_w[k];
+        c += s_c[k];
+        l = max(l, s_l[k]);
+    }
+    if (w > a.nnz) raise_err(&a.ctrl->err, ERR_BUCKET_OVERFLOW, a.rep);
+    st_ctrl(&a.ctrl->W_last, w > a.nnz ? 0 : (int32_t)w);
+    st_ctrl(&a.ctrl->fnz_last, c);
+    st_ctrl(&a.ctrl->maxlen_last, l);
+}
+
 template <int XMODE>
 __device__ __forceinline__ uint32_t x_value(const void* x_val, int p, int32_t j) {
     if constexpr (XMODE == XV_BITS32) return reinterpret_cast<const uint32_t*>(x_val)[p];
     else if constexpr (XMODE == XV_INDEX) return (uint32_t)j;
     else if constexpr (XMODE == XV_U8) return reinterpret_cast<const uint8_t*>(x_val)[p] ? 1u : 0u;
     else return 1u;
+}
+
+// The semiring's Mult of a stored entry's value and an x value.
+template <int SR>
+__device__ __forceinline__ uint32_t mult_value(float av, uint32_t xbits) {
+    if constexpr (SR == SR_PLUS_TIMES) return __float_as_uint(__fmul_rn(av, __uint_as_float(xbits)));
+    else if constexpr (SR == SR_MIN_SELECT2ND) return xbits;
+    else return (av != 0.0f ? 1u : 0u) & (xbits != 0u ? 1u : 0u);
 }
 
 template <int SR>

@@ -26,8 +26,6 @@ static_assert(kHWords * 32 * kHBlock == kHTileRows, "tile shape");
 template <int SR>
 __global__ __launch_bounds__(kHBlock) void k_hmerge_acc(MergeArgs a) {
     if (a.gate && ld_ctrl(&a.ctrl->dir) != 0) return;   // this BFS level runs pull
-    const int W = ld_ctrl(&a.ctrl->W);
-    if (W == 0) return;
     const int b = blockIdx.x / a.h_split, part = blockIdx.x - b * a.h_split;
     const int tl = a.tile_log2;
     const int64_t row0 = (int64_t)b << tl;
@@ -64,6 +62,9 @@ __global__ __launch_bounds__(kHBlock) void k_hmerge_out(MergeArgs a) {
     if (a.gate && ld_ctrl(&a.ctrl->dir) != 0) return;
     const int tid = threadIdx.x;
     const int tile = blockIdx.x;
+    // the bucket counters start the next call at zero
+    for (int i = tile * kHBlock + tid; i < a.nb; i += (int)gridDim.x * kHBlock) st_ctrl(&a.cursor[i], 0);
+    if (tile == 0 && a.stat) collect_stats<kHBlock>(a);
     const int64_t nwords = ((int64_t)a.m + 31) >> 5;
     const int64_t w0 = (int64_t)tile * (kHTileRows / 32) + (int64_t)tid * kHWords;
     uint32_t bits[kHWords];

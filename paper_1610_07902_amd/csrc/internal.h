@@ -180,10 +180,50 @@ struct ScatterArgs {
     int gate;                // 1: skip the work when ctrl->dir selects pull
 };
 
+// Expansion phase (scan and scatter in one kernel, expand_kernels.hip).
+constexpr int kLongCol = 2047;        // longest column it takes
+constexpr int kExpandMaxGrid = 4096;  // workgroups (entries of the statistics array)
+struct ExpandStat {
+    int64_t products;   // sum of the lengths of the workgroup's selected columns
+    int32_t columns;    // how many of them have entries
+    int32_t longest;
+};
+struct ExpandArgs {
+    const int32_t* colptr;   // CSC or, with dcsc, the stored columns' starts (ScanArgs)
+    int32_t n;
+    int dcsc;
+    const int32_t* dc_jc;
+    const int32_t* dc_aux;
+    int32_t dc_shift;
+    const int32_t* rowids;
+    const float* values;     // nullable (pattern)
+    const int32_t* x_idx;
+    const void* x_val;
+    int32_t f_host;          // used when f_dev == nullptr
+    const int32_t* f_dev;
+    int32_t per_tile;        // x entries per workgroup tile (f_host)
+    int32_t per_min;         // at least that many for a device-known f
+    Ctrl* ctrl;
+    int bump_level;          // BFS: advance ctrl->level when f > 0
+    int tile_log2;
+    int32_t nb;
+    int32_t m;
+    const int32_t* rcp;      // [m+1] prefix of row counts of A = bucket bases
+    int32_t* cursor;         // [nb] bucket fill counters, zero on entry (the merge leaves them so)
+    uint64_t* lb3;           // merge look-back words, cleared here
+    int32_t lb3_n;
+    uint2* buckets;          // [nnz] (row, value bits)
+    const uint32_t* mask;    // as in ScatterArgs
+    int mask_keep;
+    ExpandStat* stat;        // [grid]
+};
+size_t expand_lds_bytes(int nb, int block, int items);
+int expand_resident(int semiring, int xmode, int block, int items, int nb);
+
 // Merge + compaction phase: one workgroup per bucket.
 struct MergeArgs {
     Ctrl* ctrl;
-    const int32_t* cursor;
+    int32_t* cursor;         // read, and left zero for the next call
     const uint2* buckets;
     const int32_t* rcp;
     int32_t m;
@@ -215,6 +255,10 @@ struct MergeArgs {
     uint32_t* h_touched;
     int32_t h_split;         // workgroups per bucket in the accumulation
     Report* rep;             // nullable: where a waiting call's results go
+    // after the expansion phase: its statistics (nullable)
+    const ExpandStat* stat;
+    int32_t stat_n;
+    int64_t nnz;             // more products than stored entries mean repeated x indices
     // bitvector output (single calls, not BFS or batched): every word of y's
     // bitmap is written from the tiles' touched-row bitmaps; nullable
     uint32_t* y_bits;
@@ -411,6 +455,8 @@ struct LaunchEvents {
 hipError_t launch_scan(const ScanArgs& a, int grid, hipStream_t s, const LaunchEvents* ev = nullptr);
 hipError_t launch_scatter(const ScatterArgs& a, int semiring, int block, int items, int grid, hipStream_t s,
                           const LaunchEvents* ev = nullptr);
+hipError_t launch_expand(const ExpandArgs& a, int semiring, int xmode, int block, int items, int grid, hipStream_t s,
+                         const LaunchEvents* ev = nullptr);
 hipError_t launch_merge(const MergeArgs& a, int semiring, int block, bool bfs, hipStream_t s,
                         const LaunchEvents* ev = nullptr);
 

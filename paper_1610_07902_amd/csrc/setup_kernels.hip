@@ -36,7 +36,9 @@ __global__ void k_validate_colptr(const int32_t* colptr, int32_t n, int64_t nnz,
         if (j == 0 && a != 0) atomicOr(&ctrl->err, ERR_CSC);
         if (j == n - 1 && (int64_t)b != nnz) atomicOr(&ctrl->err, ERR_CSC);
     }
-    if (lmax > 0) atomicMax(maxout, lmax);
+    // one update per wave (an update per thread queues on the word)
+    for (int d = 32; d >= 1; d >>= 1) lmax = max(lmax, __shfl_xor(lmax, d, 64));
+    if ((threadIdx.x & 63) == 0 && lmax > 0) atomicMax(maxout, lmax);
 }
 
 __device__ int block_scan_excl(int v, int* s) {

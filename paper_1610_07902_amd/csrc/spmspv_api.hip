@@ -471,8 +471,29 @@ int64_t scatter_occupancy(const spmspv_matrix* A, int semiring, int nb, int bloc
     return occ < 1 ? 1 : occ;
 }
 
-// Enqueue the three phases of one y <- A x.
-// phases: 1 = scan only, 2 = scatter + merge only, 3 = all.  tile_log2 < 0
+// How the expansion phase cuts f x entries into workgroup tiles.
+struct ExpandTiles {
+    int per;    // x entries per tile
+    int grid;   // workgroups
+};
+ExpandTiles expand_tiles(int64_t n, int64_t nnz, int64_t f, int block, int chunk, int gmax) {
+    const double d = std::max(1.0, n > 0 ? (double)nnz / (double)n : 1.0);   // products per x entry, on average
+    // one chunk's worth, with room for uneven columns
+    const int64_t one = std::max<int64_t>(1, (int64_t)(0.85 * chunk / d));
+    int64_t per = (f + gmax - 1) / gmax;                // a tile per workgroup
+    if (per > one) per = (per + one - 1) / one * one;   // or several chunks per tile
+    per = std::max<int64_t>(per, std::min<int64_t>(16, block));
+    per = std::min<int64_t>(per, block);
+    ExpandTiles t;
+    t.per = (int)per;
+    t.grid = (int)std::max<int64_t>(1, std::min<int64_t>((f + per - 1) / per, gmax));
+    return t;
+}
+
+// Enqueue the phases of one y <- A x: expansion and merge, or with columns too
+// long for the expansion or a decision in between (direction switching,
+// selector) scan, scatter and merge.
+// phases: 1 = scan only, 2 = scatter + merge only (after a scan), 3 = all.  tile_log2 < 0
 // uses the handle's schedule.  clear_nb > 0 makes the scan clear that many
 // bucket counters (so a later scatter may use a narrower tile).
 int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int32_t* f_dev, const int32_t* x_idx,
@@ -587,9 +608,11 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
     if (wbound > A->nnz) wbound = A->nnz;
     int64_t g2 = (wbound + chunk - 1) / chunk;
     if (g2 < 1) g2 = 1;
-    const int64_t g2max =
-        int64_t(A->num_cu) * scatter_occupancy(A, semiring, nb, sc.scatter_block, sc.scatter_items, false);
-    if (g2 > g2max) g2 = g2max;
+    // scan and scatter in one kernel where no column is too long for its tiles
+    const bool fused = phases == 3 && !diropt && Omaxdeg <= kLongCol;
+    if (!fused && (phases & 2))
+        g2 = std::min(g2, int64_t(A->num_cu) *
+                              scatter_occupancy(A, semiring, nb, sc.scatter_block, sc.scatter_items, false));
 
     MergeArgs ma{};
     ma.ctrl = A->ctrl;
@@ -620,6 +643,51 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
     const LaunchEvents le[3] = {{ev ? ev[0] : nullptr, ev ? ev[1] : nullptr},
                                 {ev ? ev[2] : nullptr, ev ? ev[3] : nullptr},
                                 {ev ? ev[4] : nullptr, ev ? ev[5] : nullptr}};
+    if (fused) {
+        ExpandArgs ea{};
+        ea.colptr = sa.colptr;
+        ea.n = sa.n;
+        ea.dcsc = sa.dcsc;
+        ea.dc_jc = sa.dc_jc;
+        ea.dc_aux = sa.dc_aux;
+        ea.dc_shift = sa.dc_shift;
+        ea.rowids = Orowids;
+        ea.values = Ovalues;
+        ea.x_idx = x_idx;
+        ea.x_val = x_val;
+        ea.f_host = (int32_t)f_host;
+        ea.f_dev = f_dev;
+        ea.ctrl = A->ctrl;
+        ea.bump_level = sa.bump_level;
+        ea.tile_log2 = sc.tile_log2;
+        ea.nb = nb;
+        ea.m = (int32_t)Om;
+        ea.rcp = Orcp;
+        ea.cursor = A->cursor;
+        ea.lb3 = A->lb3;
+        ea.lb3_n = sa.nb;
+        ea.buckets = A->buckets;
+        ea.mask = mask;
+        ea.mask_keep = mask_keep;
+        // scratch of the one-launch multiply, which this call is not
+        static_assert(size_t(kExpandMaxGrid) * sizeof(ExpandStat) <= size_t(kFMaxGrid) * kFSamples * 4, "stat array");
+        ea.stat = reinterpret_cast<ExpandStat*>(A->ws + A->L.samples);
+        const int gmax = (int)std::min<int64_t>(
+            kExpandMaxGrid, (int64_t)A->num_cu * expand_resident(semiring, xmode, sc.scatter_block, sc.scatter_items, nb));
+        const ExpandTiles et = expand_tiles(On, A->nnz, f_host, sc.scatter_block, chunk, gmax);
+        ea.per_tile = et.per;
+        ea.per_min = std::min(sc.scatter_block, 16);
+        const int grid = f_dev ? gmax : et.grid;
+        ma.stat = ea.stat;
+        ma.stat_n = grid;
+        ma.nnz = A->nnz;
+        if (ev) {   // no scan kernel: its phase is the empty interval before this one
+            HIP_TRY(hipEventRecord(ev[0], s));
+            HIP_TRY(hipEventRecord(ev[1], s));
+        }
+        HIP_TRY(launch_expand(ea, semiring, xmode, sc.scatter_block, sc.scatter_items, grid, s, ev ? &le[1] : nullptr));
+        phases = 4;   // the merge is left
+    }
     if (phases & 1) {
         HIP_TRY(launch_scan(sa, (int)g1, s, ev ? &le[0] : nullptr));
         if (diropt && learned_gate)   // the selector picks the direction on the device
@@ -627,8 +695,9 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
         else if (diropt)
             HIP_TRY(launch_decide(A->ctrl, (int32_t)A->n, A->nnz, s));
     }
-    if (phases & 2) {
+    if (phases & 2)
         HIP_TRY(launch_scatter(ca, semiring, sc.scatter_block, sc.scatter_items, (int)g2, s, ev ? &le[1] : nullptr));
+    if (phases & 6) {
         if (hbm) {   // two kernels: profile them between plain event markers
             if (ev) HIP_TRY(hipEventRecord(ev[4], s));
             HIP_TRY(launch_hbm_merge(ma, semiring, bfs, s));
@@ -1197,10 +1266,12 @@ hipError_t reset_persistent_state(spmspv_matrix* A, hipStream_t s) {
     return launch_fill_u64(reinterpret_cast<uint64_t*>(A->ws + A->L.h_f64), 0x8000000000000000ull, A->L.h_rows, s);
 }
 
-// Clears the sticky error bits, and the persistent BFS words, which a launch
+// Clears the sticky error bits, the bucket counters (a call that gave up may
+// leave them in use) and the persistent BFS words, which a launch
 // that gave up at a barrier leaves as they were.
 int clear_err(spmspv_matrix* A, hipStream_t s) {
     HIP_TRY(launch_fill_u32(&A->ctrl->err, 0u, 1, s));
+    HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(A->cursor), 0u, A->L.nb_max, s));
     HIP_TRY(reset_persistent_state(A, s));
     return SPMSPV_OK;
 }

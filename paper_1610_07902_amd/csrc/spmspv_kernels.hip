@@ -330,11 +330,14 @@ enum { SC_SINGLE = 0, SC_COUNT = 1, SC_BATCH = 2 };
 template <int BLOCK, int ITEMS, int SR, int MODE>
 __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
     constexpr int C = BLOCK * ITEMS;
-    extern __shared__ uint32_t lds_scatter[];
+    extern __shared__ __align__(16) uint32_t lds_scatter[];
     const int nb = a.nb;
-    int32_t* hist = reinterpret_cast<int32_t*>(lds_scatter);   // [nb] counts, then global slot base
-    int32_t* loff = hist + nb;                                  // [nb] chunk-local bucket offsets
-    uint32_t* region = lds_scatter + 2 * nb + 2;                // 8-byte aligned
+    constexpr int WORDS = C / 32;   // column-start bits of a chunk
+    int32_t* hist = reinterpret_cast<int32_t*>(lds_scatter);   // [nb + 64] counts, then global slot base
+    int32_t* loff = hist + nb + kWave;                          // [nb] chunk-local bucket offsets
+    uint32_t* bits = reinterpret_cast<uint32_t*>(loff + nb);    // [WORDS] column starts in the chunk
+    int32_t* pre = reinterpret_cast<int32_t*>(bits + WORDS);    // [WORDS] columns before each word
+    uint32_t* region = lds_scatter + 2 * nb + kWave + 2 * WORDS;   // 8-byte aligned
     // Column table (phase 1): product offset of each column inside the chunk
     // (16 bits: the first column is cut to start at the chunk, the others
     // start inside it), its first entry in A and its x value.
@@ -342,11 +345,11 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
     int32_t* s_start = reinterpret_cast<int32_t*>(s_off + (C + 2));
     uint32_t* s_xv = reinterpret_cast<uint32_t*>(s_start + (C + 1));
     int32_t* s_xid = reinterpret_cast<int32_t*>(s_xv + (C + 1)); // batched: vector of each column
-    uint16_t* col_of = reinterpret_cast<uint16_t*>(s_xv + (MODE != SC_SINGLE ? 2 : 1) * (C + 1));   // [C] (phase 1)
-    uint2* stage = reinterpret_cast<uint2*>(region);            // [C] sort buffer (phase 3)
-    int32_t* skey = reinterpret_cast<int32_t*>(stage + C);      // batched: [C] key of each staged entry
+    uint2* stage = reinterpret_cast<uint2*>(region);            // [C + 64] sort buffer (phase 3)
+    int32_t* skey = reinterpret_cast<int32_t*>(stage + C + kWave);   // batched: [C + 64] key of each staged entry
     __shared__ int s_tmp[BLOCK / kWave + 1];
     const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
 
     // The control words, loaded together: one round trip before the work
     // instead of one per word.
@@ -374,8 +377,22 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
     const int nchunks = (int)(((int64_t)W + C - 1) / C);
     if ((int)blockIdx.x >= nchunks) return;
 
-    for (int i = tid; i < nb; i += BLOCK) hist[i] = 0;
+    for (int i = tid; i < nb + kWave; i += BLOCK) hist[i] = 0;
+    for (int i = tid; i < WORDS; i += BLOCK) bits[i] = 0u;
     const int tl = a.tile_log2;
+    // the slots [base, top) of the bucket this thread reserves for
+    int base = 0, top = 0;
+    const bool counted = MODE == SC_BATCH && a.xstride == 0;   // bases from the counting pass
+    if (MODE != SC_COUNT && nb <= BLOCK && tid < nb) {
+        if (counted) {
+            base = a.kbase[tid];
+            top = a.kbase[tid + 1];
+        } else {   // row-count prefix (inside the vector's slice for fixed batched bases)
+            const int r0 = (MODE == SC_BATCH ? tid - (tid / a.nbx) * a.nbx : tid) << tl;
+            base = a.rcp[r0];
+            top = a.rcp[(int)min((int64_t)r0 + (int64_t(1) << tl), (int64_t)a.m)];
+        }
+    }
 
     for (int c = blockIdx.x; c < nchunks; c += gridDim.x) {
         const int q0 = c * C;
@@ -383,14 +400,34 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
         const int p0 = a.chunk_col[c];
         const int pend = (c + 1 < nchunks) ? a.chunk_col[c + 1] : fnz - 1;
         const int ncols = pend - p0 + 1;
-        __syncthreads();  // the previous chunk is done with hist, loff and the shared region
+        __syncthreads();  // the previous chunk is done with hist, loff and the shared region; the bits are clear
         for (int k = tid; k < ncols; k += BLOCK) {
             const int off = a.coff[p0 + k] - q0;   // <= 0 only for k == 0
             const int st = a.cstart[p0 + k];
-            s_off[k] = (uint16_t)(k == 0 ? 0 : off);
+            const int o = k == 0 ? 0 : off;
+            s_off[k] = (uint16_t)o;
             s_start[k] = k == 0 ? st - off : st;
             s_xv[k] = a.cxv[p0 + k];
             if constexpr (MODE != SC_SINGLE) s_xid[k] = a.cxid[p0 + k];
+            if (o < C) atomicOr(&bits[o >> 5], 1u << (o & 31));   // o == C: the next chunk's first column
+        }
+        __syncthreads();
+        if (tid < kWave) {   // columns before each word
+            constexpr int PER = WORDS / kWave > 0 ? WORDS / kWave : 1;
+            int p[PER], sum = 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int w = lane * PER + i;
+                p[i] = w < WORDS ? __popc(bits[w]) : 0;
+                sum += p[i];
+            }
+            int run = wave_inclusive_i32(sum) - sum;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int w = lane * PER + i;
+                if (w < WORDS) pre[w] = run;
+                run += p[i];
+            }
         }
         __syncthreads();
         // Keys this chunk can touch: every bucket of a single call; in a
@@ -403,64 +440,84 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
             khi = min(nb, (s_xid[ncols - 1] + 1) * a.nbx);
         }
 
-        // (1) gather + rank.  Column map: each thread finds the column of
-        // its ITEMS consecutive products (one binary search, then a forward
-        // walk) and records it in LDS.  Products are then taken strided
-        // (item i of thread t is product i * BLOCK + t), so the lanes of a
-        // wave read consecutive row ids and values: one request per cache
-        // line instead of one per lane.  All row-id / value / mask loads are
-        // issued together (indices clamped into range); ranks are taken in
-        // LDS.
-        int32_t row[ITEMS], rank[ITEMS], qq[ITEMS], xid[ITEMS];
-        uint32_t xcol[ITEMS];
+        // (1) gather + rank, lanes on consecutive products: one request per
+        // cache line instead of one per lane.  Product k's column is the
+        // number of column starts up to k.  Every load, LDS atomic and LDS
+        // read is unconditional (a product past the chunk or dropped by the
+        // mask counts in a counter of its lane's own and is sorted to a slot
+        // of its lane's own), and each group is issued as a whole before its
+        // first use: left to the compiler, conditions become branches and the
+        // groups chains of single LDS round trips.  What bounds the kernel:
+        // the counter adds of (2) (about 25 per ns for the whole chip), then
+        // the LDS traffic of the sort, whose 8-byte entries must be 8-byte
+        // aligned: with the dynamic LDS starting at a multiple of 4 every
+        // access was split, 18.6 us at scale 22, 1 % and 103 at 10 % against
+        // 14.2 and 77.8 (50 without the adds).
+        int32_t row[ITEMS], slot[ITEMS], xid[ITEMS];
+        uint32_t val[ITEMS];
+        bool ok[ITEMS];
         {
-            const int rq0 = tid * ITEMS;
-            int lo = 0, hi = ncols - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (s_off[mid] <= rq0) lo = mid; else hi = mid - 1;
-            }
-            int next = lo + 1 < ncols ? s_off[lo + 1] : 0x7fffffff;
+            int32_t col[ITEMS], before[ITEMS], st[ITEMS], of[ITEMS], q[ITEMS];
+            uint32_t word[ITEMS], xcol[ITEMS];
 #pragma unroll
             for (int i = 0; i < ITEMS; ++i) {
-                const int rq = rq0 + i;
-                while (rq >= next) {
-                    ++lo;
-                    next = lo + 1 < ncols ? s_off[lo + 1] : 0x7fffffff;
-                }
-                if (rq < cnt) col_of[rq] = (uint16_t)lo;
+                const int k = i * BLOCK + tid;
+                word[i] = bits[k >> 5];
+                before[i] = pre[k >> 5];
             }
+            loaded(word);
+            loaded(before);
+            const uint32_t upto = (2u << (tid & 31)) - 1u;
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                ok[i] = i * BLOCK + tid < cnt;
+                col[i] = ok[i] ? before[i] + __popc(word[i] & upto) - 1 : 0;
+            }
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                st[i] = s_start[col[i]];
+                of[i] = s_off[col[i]];
+                xcol[i] = s_xv[col[i]];
+                xid[i] = MODE != SC_SINGLE ? s_xid[col[i]] : 0;
+            }
+            loaded(st);
+            loaded(of);
+            loaded(xcol);
+            if constexpr (MODE != SC_SINGLE) loaded(xid);
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) q[i] = ok[i] ? st[i] + (i * BLOCK + tid - of[i]) : 0;
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) row[i] = a.rowids[q[i]];
+            if constexpr (MODE != SC_COUNT) {
+                if (SR != SR_MIN_SELECT2ND && a.values) {
+                    float av[ITEMS];
+#pragma unroll
+                    for (int i = 0; i < ITEMS; ++i) av[i] = a.values[q[i]];
+                    loaded(av);
+#pragma unroll
+                    for (int i = 0; i < ITEMS; ++i) val[i] = mult_value<SR>(av[i], xcol[i]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < ITEMS; ++i) val[i] = mult_value<SR>(1.0f, xcol[i]);
+                }
+            }
+            loaded(row);
         }
-        __syncthreads();
+        if (a.mask) {
+            uint32_t mw[ITEMS];
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const int k = i * BLOCK + tid;
-            const int lo = k < cnt ? col_of[k] : 0;
-            qq[i] = k < cnt ? s_start[lo] + (k - s_off[lo]) : -1;
-            xcol[i] = s_xv[lo];
-            xid[i] = MODE != SC_SINGLE ? s_xid[lo] : 0;
+            for (int i = 0; i < ITEMS; ++i) mw[i] = a.mask[(int64_t)xid[i] * a.mask_words + ((uint32_t)row[i] >> 5)];
+            loaded(mw);
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) ok[i] = ok[i] && ((mw[i] >> (row[i] & 31)) & 1u) == (uint32_t)a.mask_keep;
         }
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) row[i] = a.rowids[qq[i] >= 0 ? qq[i] : 0];
-        uint32_t val[ITEMS];
-        if constexpr (MODE != SC_COUNT) {
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i) val[i] = mult<SR>(a.values, qq[i] >= 0 ? qq[i] : 0, xcol[i]);
-        }
-        uint32_t mw[ITEMS];
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i)
-            mw[i] = a.mask ? a.mask[(int64_t)xid[i] * a.mask_words + ((uint32_t)row[i] >> 5)] : 0u;
-        // A product's bucket (key) is recomputed from its row where needed;
-        // rank < 0 marks a product that is dropped (past the chunk, masked).
+        // A product's bucket (key) is recomputed from its row where needed.
         auto bucket = [&](int i) { return MODE != SC_SINGLE ? xid[i] * a.nbx + (row[i] >> tl) : row[i] >> tl; };
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            rank[i] = -1;
-            if (qq[i] >= 0 && (!a.mask || ((mw[i] >> (row[i] & 31)) & 1u) == (uint32_t)a.mask_keep))
-                rank[i] = atomicAdd(&hist[bucket(i)], 1);
-        }
+        for (int i = 0; i < ITEMS; ++i) slot[i] = atomicAdd(&hist[ok[i] ? bucket(i) : nb + lane], 1);
+        loaded(slot);
         __syncthreads();
+        for (int i = tid; i < WORDS; i += BLOCK) bits[i] = 0u;
         if constexpr (MODE == SC_COUNT) {
             // Algorithm 2's per-bucket counts, accumulated over workgroups.
             for (int b = klo + tid; b < khi; b += BLOCK) {
@@ -472,6 +529,19 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
             }
             continue;   // the loop head synchronises before hist is reused
         }
+        // (3) counting sort into the LDS buffer
+        auto sort = [&]() {
+            int32_t o[ITEMS];
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) o[i] = loff[ok[i] ? bucket(i) : 0];
+            loaded(o);
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                const int at = ok[i] ? o[i] + slot[i] : C + lane;
+                stage[at] = make_uint2((uint32_t)row[i], val[i]);
+                if constexpr (MODE == SC_BATCH) skey[at] = bucket(i);
+            }
+        };
         // (2) chunk-local offsets and one slot reservation per touched
         // bucket.  With at most one bucket per thread (the usual case) the
         // reservation's round trip overlaps the counting sort (3), which
@@ -481,33 +551,18 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
             const int b = tid;
             const int n = b < nb ? hist[b] : 0;
             const int e = block_exclusive_i32<BLOCK>(n, s_tmp, kept);
-            int base = 0, top = 0, g = 0;   // the bucket's slots are [base, top)
+            int g[1] = {0};
             if (b < nb) loff[b] = e;
-            if (n > 0) {
-                g = atomicAdd(&a.cursor[b], n);
-                if (MODE == SC_BATCH && a.xstride == 0) {
-                    base = a.kbase[b];
-                    top = a.kbase[b + 1];
-                } else {
-                    const int r0 = (MODE == SC_BATCH ? b - (b / a.nbx) * a.nbx : b) << tl;
-                    base = a.rcp[r0];
-                    top = a.rcp[min(r0 + (1 << tl), a.m)];
-                }
-            }
+            if (n > 0) g[0] = atomicAdd(&a.cursor[b], n);
             __syncthreads();
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i)
-                if (rank[i] >= 0) {
-                    const int bi = bucket(i);
-                    stage[loff[bi] + rank[i]] = make_uint2((uint32_t)row[i], val[i]);
-                    if constexpr (MODE == SC_BATCH) skey[loff[bi] + rank[i]] = bi;
-                }
+            sort();
+            loaded(g);   // not before the sort
             if (n > 0) {
-                if (base + g + n > top) {
+                if (base + g[0] + n > top) {
                     atomicOr(&a.ctrl->err, ERR_BUCKET_OVERFLOW);
                     hist[b] = -1;
                 } else {
-                    hist[b] = base + g;
+                    hist[b] = base + g[0];
                 }
             }
             __syncthreads();
@@ -521,21 +576,21 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
                 if (b < khi) {
                     loff[b] = carry + e;
                     if (n > 0) {
-                        int base, cap;
-                        if (MODE == SC_BATCH && a.xstride == 0) {
-                            base = a.kbase[b];
-                            cap = a.kbase[b + 1] - base;
-                        } else {   // row-count prefix (inside the vector's slice for fixed batched bases)
+                        int kb, cap;
+                        if (counted) {
+                            kb = a.kbase[b];
+                            cap = a.kbase[b + 1] - kb;
+                        } else {
                             const int r0 = (MODE == SC_BATCH ? b - (b / a.nbx) * a.nbx : b) << tl;
-                            base = a.rcp[r0];
-                            cap = a.rcp[min(r0 + (1 << tl), a.m)] - base;
+                            kb = a.rcp[r0];
+                            cap = a.rcp[(int)min((int64_t)r0 + (int64_t(1) << tl), (int64_t)a.m)] - kb;
                         }
                         const int g = atomicAdd(&a.cursor[b], n);
                         if (g + n > cap) {
                             atomicOr(&a.ctrl->err, ERR_BUCKET_OVERFLOW);
                             hist[b] = -1;
                         } else {
-                            hist[b] = base + g;
+                            hist[b] = kb + g;
                         }
                     }
                 }
@@ -543,28 +598,37 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
             }
             kept = carry;
             __syncthreads();
-            // (3) counting sort into the LDS buffer
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i)
-                if (rank[i] >= 0) {
-                    const int bi = bucket(i);
-                    stage[loff[bi] + rank[i]] = make_uint2((uint32_t)row[i], val[i]);
-                    if constexpr (MODE == SC_BATCH) skey[loff[bi] + rank[i]] = bi;
-                }
+            sort();
             __syncthreads();
         }
         // (4) coalesced write-out of the bucket runs
-        for (int t = tid; t < kept; t += BLOCK) {
-            const uint2 e = stage[t];
-            const int b = MODE == SC_BATCH ? skey[t] : (int)e.x >> tl;
-            const int gb = hist[b];
-            const int64_t slice = (MODE == SC_BATCH && a.xstride) ? (int64_t)(b / a.nbx) * a.xstride : 0;
-            if (gb >= 0) a.buckets[slice + gb + (t - loff[b])] = e;
+        {
+            uint2 e[ITEMS];
+            int key[ITEMS], gb[ITEMS], lo[ITEMS];
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                e[i] = stage[i * BLOCK + tid];
+                if constexpr (MODE == SC_BATCH) key[i] = skey[i * BLOCK + tid];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                if constexpr (MODE != SC_BATCH) key[i] = (int)e[i].x >> tl;
+                if (i * BLOCK + tid >= kept) key[i] = klo;
+                gb[i] = hist[key[i]];
+                lo[i] = loff[key[i]];
+            }
+            loaded(gb);
+            loaded(lo);
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) {
+                const int t = i * BLOCK + tid;
+                const int64_t slice = (MODE == SC_BATCH && a.xstride) ? (int64_t)(key[i] / a.nbx) * a.xstride : 0;
+                if (t < kept && gb[i] >= 0) a.buckets[slice + gb[i] + (t - lo[i])] = e[i];
+            }
         }
         __syncthreads();
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i)
-            if (rank[i] == 0) hist[bucket(i)] = 0;
+        for (int b = klo + tid; b < khi; b += BLOCK) hist[b] = 0;
     }
 }
 
@@ -584,9 +648,17 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
 // the look-back runs over all keys, so y holds the vectors' results one
 // after another (each ascending) and the first bucket of each vector
 // publishes where its part starts (yoff).
+__device__ __forceinline__ void publish_total(const MergeArgs& a, int64_t total, bool batch) {
+    a.ctrl->nnz_y = total;
+    if (a.d_nnz_y) *a.d_nnz_y = total;
+    report_nnz(a.rep, a.ctrl, total);
+    if (a.set_f) st_ctrl(&a.ctrl->f, (int32_t)total);
+    if (batch) a.yoff[a.nbatch] = total;
+}
+
 template <int BLOCK, int ITEMS, int SR, bool BFS, bool BATCH>
 __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
-    extern __shared__ uint32_t lds_merge[];
+    extern __shared__ __align__(16) uint32_t lds_merge[];
     const int tl = a.tile_log2;
     const int T = 1 << tl;
     constexpr bool kWide = SR == SR_PLUS_TIMES;                      // fp64 cells
@@ -607,7 +679,6 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
         bt = b - xb * a.nbx;
     }
     const int row0 = bt << tl;
-    const int W = ld_ctrl(&a.ctrl->W);
     const int cnt_raw = ld_ctrl(&a.cursor[b]);
     int64_t base;
     int cap;
@@ -619,31 +690,24 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
         cap = a.rcp[min(row0 + T, a.m)] - a.rcp[row0];
     }
     __syncthreads();
-    // a tile with no entries still writes its (empty) words of y's bitmap
-    auto zero_bits = [&]() {
-        if (!BFS && !BATCH && a.y_bits) {
-            const int zw = (min(T, a.m - row0) + 31) >> 5;
-            for (int w = tid; w < zw; w += BLOCK) a.y_bits[(row0 >> 5) + w] = 0u;
-        }
-    };
-    if (W == 0) {
-        zero_bits();
-        if (tid == 0) {
-            if (BATCH && bt == 0) a.yoff[xb] = 0;
-            if (b == a.nb - 1) {
-                a.ctrl->nnz_y = 0;
-                if (a.d_nnz_y) *a.d_nnz_y = 0;
-                report_nnz(a.rep, a.ctrl, 0);
-                if (a.set_f) st_ctrl(&a.ctrl->f, 0);
-                if (BATCH) a.yoff[a.nbatch] = 0;
-            }
-        }
-        return;
-    }
+    if (tid == 0 && cnt_raw != 0) st_ctrl(&a.cursor[b], 0);
     const int rows = min(T, a.m - row0);
-    if (cnt_raw == 0 && b != a.nb - 1 && (!BATCH || bt != 0)) {
-        zero_bits();
-        if (tid == 0) st_release64(&a.lb3[b], (b == 0 ? LB_INC : LB_AGG));
+    if (cnt_raw == 0) {
+        // an empty tile writes its (empty) words of y's bitmap, and publishes
+        // where its vector or the whole of y starts or ends
+        if (!BFS && !BATCH && a.y_bits)
+            for (int w = tid; w < (rows + 31) >> 5; w += BLOCK) a.y_bits[(row0 >> 5) + w] = 0u;
+        const bool last = b == a.nb - 1;
+        if (tid < kWave && (last || (BATCH && bt == 0))) {
+            const uint64_t e = lookback(a.lb3, b, 0ull, &a.ctrl->err, a.rep);
+            if (tid == 0) {
+                if (BATCH && bt == 0) a.yoff[xb] = (int64_t)e;
+                if (last) publish_total(a, (int64_t)e, BATCH);
+            }
+        } else if (tid == 0) {
+            st_release64(&a.lb3[b], (b == 0 ? LB_INC : LB_AGG));
+        }
+        if (!BATCH && b == 0 && a.stat) collect_stats<BLOCK>(a);
         return;
     }
     // Slots past the bucket's capacity exist only after an overflow
@@ -727,14 +791,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
         if (tid == 0) {
             s_excl = (int64_t)e;
             if (BATCH && bt == 0) a.yoff[xb] = (int64_t)e;
-            if (b == a.nb - 1) {
-                const int64_t total = (int64_t)e + ucnt;
-                a.ctrl->nnz_y = total;
-                if (a.d_nnz_y) *a.d_nnz_y = total;
-                report_nnz(a.rep, a.ctrl, total);
-                if (a.set_f) st_ctrl(&a.ctrl->f, (int32_t)total);
-                if (BATCH) a.yoff[a.nbatch] = total;
-            }
+            if (b == a.nb - 1) publish_total(a, (int64_t)e + ucnt, BATCH);
         }
     }
     __syncthreads();
@@ -788,6 +845,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
         carry += tot;
         __syncthreads();
     }
+    if (!BATCH && b == 0 && a.stat) collect_stats<BLOCK>(a);
 }
 
 }  // namespace
@@ -799,10 +857,10 @@ size_t merge_lds_bytes(int tile_log2, int semiring) {
 }
 
 size_t scatter_lds_bytes(int nb, int chunk, bool batch) {
-    // column table (+ the per-product column map) in phase 1, sort buffer in phase 3
-    const size_t table = size_t(chunk + 2) * 2 + size_t(chunk + 1) * (batch ? 12 : 8) + size_t(chunk) * 2,
-                 sortbuf = size_t(chunk) * (batch ? 12 : 8);
-    return size_t(2 * nb + 2) * 4 + (table > sortbuf ? table : sortbuf);
+    // column table in phase 1, sort buffer in phase 3
+    const size_t table = size_t(chunk + 2) * 2 + size_t(chunk + 1) * (batch ? 12 : 8),
+                 sortbuf = size_t(chunk + kWave) * (batch ? 12 : 8);
+    return (size_t(2 * nb) + kWave + chunk / 16) * 4 + (table > sortbuf ? table : sortbuf);
 }
 
 template <typename K>
