@@ -59,38 +59,52 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
 
 // Decoupled look-back over per-tile state words (status in bits 63:62,
 // value in 61:0).  Called by all 64 lanes of one wave.  Publishes `agg` for
-// `tile`, returns the exclusive prefix and publishes the inclusive one.
+// `tile`, returns the exclusive prefix and publishes the inclusive one.  K
+// words per lane and round trip: predecessors that all finish at about the
+// same time leave only sums, which one round of 64 * K covers.
 // A wait that exceeds kSpinMax polls sets ERR_SPIN and returns a partial
 // prefix rather than hanging.
+__device__ __forceinline__ void publish_sum(uint64_t* st, int tile, uint64_t agg) {
+    st_release64(&st[tile], (tile == 0 ? LB_INC : LB_AGG) | (agg & LB_VAL));
+}
+
+template <int K = 1>
 __device__ inline uint64_t lookback(uint64_t* st, int tile, uint64_t agg, uint32_t* err, Report* rep = nullptr) {
     const int lane = threadIdx.x & (kWave - 1);
-    if (tile == 0) {
-        if (lane == 0) st_release64(&st[0], LB_INC | (agg & LB_VAL));
-        return 0;
-    }
-    if (lane == 0) st_release64(&st[tile], LB_AGG | (agg & LB_VAL));
+    if (lane == 0) publish_sum(st, tile, agg);
+    if (tile == 0) return 0;
     uint64_t excl = 0;
     int base = tile - 1;
     int spins = 0;
-    for (;;) {
-        const int idx = base - lane;
-        const uint64_t w = idx >= 0 ? ld_acquire64(&st[idx]) : LB_INC;
-        const uint64_t status = w >> 62;
-        const uint64_t inc_mask = __ballot(status == 2);
-        const uint64_t empty_mask = __ballot(status == 0);
-        const uint64_t need = inc_mask ? (((inc_mask & (~inc_mask + 1)) << 1) - 1) : ~0ull;
-        if (empty_mask & need) {
-            if (++spins > kSpinMax) {
-                if (lane == 0) raise_err(err, ERR_SPIN, rep);
+    for (bool done = false; !done;) {
+        uint64_t w[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int idx = base - k * kWave - lane;
+            w[k] = idx >= 0 ? ld_acquire64(&st[idx]) : LB_INC;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint64_t status = w[k] >> 62;
+            const uint64_t inc_mask = __ballot(status == 2);
+            const uint64_t empty_mask = __ballot(status == 0);
+            const uint64_t need = inc_mask ? (((inc_mask & (~inc_mask + 1)) << 1) - 1) : ~0ull;
+            if (empty_mask & need) {   // not there yet: look again from here
+                if (++spins > kSpinMax) {
+                    if (lane == 0) raise_err(err, ERR_SPIN, rep);
+                    done = true;
+                }
+                __builtin_amdgcn_s_sleep(1);
                 break;
             }
-            __builtin_amdgcn_s_sleep(1);
-            continue;
+            const uint64_t v = ((need >> lane) & 1ull) ? (w[k] & LB_VAL) : 0ull;
+            excl += wave_sum_u64(v);
+            if (inc_mask) {
+                done = true;
+                break;
+            }
+            base -= kWave;
         }
-        const uint64_t v = ((need >> lane) & 1ull) ? (w & LB_VAL) : 0ull;
-        excl += wave_sum_u64(v);
-        if (inc_mask) break;
-        base -= kWave;
     }
     if (lane == 0) st_release64(&st[tile], LB_INC | ((excl + agg) & LB_VAL));
     return excl;
@@ -272,50 +286,143 @@ __device__ __forceinline__ void store_value(void* y_val, int64_t o, uint32_t v) 
 // atomics and set the bitmap bit with every entry.
 constexpr uint64_t kNegZero64 = 0x8000000000000000ull;
 
-// mark: plus-times sets every entry's bitmap bit here (a bucket with few
-// entries, where one atomic per entry is cheaper than the ballot pass over
-// the whole tile); otherwise only -0.0 products set it and touched_bits64
-// finds the rest.
+// The adds alone, for rows whose bits are set already.
 template <int SR, int K>
-__device__ __forceinline__ void add_rows(const uint32_t (&r)[K], const uint32_t (&v)[K], const bool (&ok)[K],
-                                         uint32_t* spa, uint32_t* bm, bool mark = false) {
-    if constexpr (SR == SR_PLUS_TIMES) {
-        double* spa64 = reinterpret_cast<double*>(spa);
+__device__ __forceinline__ void add_values(const uint32_t (&r)[K], const uint32_t (&v)[K], const bool (&ok)[K],
+                                           uint32_t* spa) {
 #pragma unroll
-        for (int u = 0; u < K; ++u) {
-            if (ok[u]) {
-                atomicAdd(&spa64[r[u]], (double)__uint_as_float(v[u]));
-                if (mark || v[u] == 0x80000000u) atomicOr(&bm[r[u] >> 5], 1u << (r[u] & 31u));
-            }
-        }
-    } else {
-#pragma unroll
-        for (int u = 0; u < K; ++u) {
-            if (ok[u]) {
-                atomicOr(&bm[r[u] >> 5], 1u << (r[u] & 31u));
-                accumulate<SR>(&spa[r[u]], v[u]);
-            }
-        }
+    for (int u = 0; u < K; ++u) {
+        if (!ok[u]) continue;
+        if constexpr (SR == SR_PLUS_TIMES)
+            atomicAdd(&reinterpret_cast<double*>(spa)[r[u]], (double)__uint_as_float(v[u]));
+        else accumulate<SR>(&spa[r[u]], v[u]);
     }
 }
 
+// Adds and bitmap bits of a long bucket, without a branch per entry: a lane
+// that has none adds the neutral value to one of the first 32 cells.
+// mark: plus-times sets every entry's bit here (a bucket with few entries,
+// where one atomic per entry is cheaper than the ballot pass over the whole
+// tile); otherwise only those of -0.0 products, and touched_bits64 finds the
+// rest.
+template <int SR, int K>
+__device__ __forceinline__ void add_rows(const uint32_t (&r)[K], const uint32_t (&v)[K], const bool (&ok)[K],
+                                         uint32_t* spa, uint32_t* bm, bool mark = false) {
+    constexpr bool kSum = SR == SR_PLUS_TIMES;
+    const uint32_t kNone = kSum ? 0x80000000u : identity<SR>();
+    bool bits = !kSum || mark;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const uint32_t c = ok[u] ? r[u] : threadIdx.x & 31u;
+        const uint32_t w = ok[u] ? v[u] : kNone;
+        if constexpr (kSum) {
+            atomicAdd(&reinterpret_cast<double*>(spa)[c], (double)__uint_as_float(w));
+            bits |= ok[u] & (v[u] == kNone);
+        } else {
+            accumulate<SR>(&spa[c], w);
+        }
+    }
+    if (!__any(bits)) return;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const uint32_t c = ok[u] ? r[u] : threadIdx.x & 31u;
+        atomicOr(&bm[c >> 5], ok[u] & (!kSum | mark | (v[u] == kNone)) ? 1u << (c & 31u) : 0u);
+    }
+}
+
+// One row's entries, summed in a register per lane instead of in the row's
+// LDS cell.  Lanes of a wave that add to one cell wait for each other, and a
+// hub row brings a good part of every wave's lanes there.
+template <int SR>
+struct HubSum {
+    uint32_t row = ~0u;   // matches no row
+    bool any = false;     // this lane took an entry
+    uint32_t acc = identity<SR>();
+    double sum = -0.0;
+
+    // Takes the row's entries out of r, v, ok.  -0.0 products stay with the
+    // cells, where they set the row's bit.
+    template <int K>
+    __device__ __forceinline__ void take(const uint32_t (&r)[K], const uint32_t (&v)[K], bool (&ok)[K]) {
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            bool hit = ok[u] & (r[u] == row);
+            if constexpr (SR == SR_PLUS_TIMES) {
+                hit &= v[u] != 0x80000000u;
+                sum += hit ? (double)__uint_as_float(v[u]) : -0.0;
+            } else if constexpr (SR == SR_MIN_SELECT2ND) {
+                acc = hit ? (uint32_t)min((int)acc, (int)v[u]) : acc;
+            } else {
+                acc |= hit ? v[u] : 0u;
+            }
+            any |= hit;
+            ok[u] &= !hit;
+        }
+    }
+    // adds what the wave's lanes took to the row (all 64 lanes)
+    __device__ __forceinline__ void flush(uint32_t* spa, uint32_t* bm) {
+        if (!__any(any)) return;
+        const int lane = threadIdx.x & (kWave - 1);
+        if constexpr (SR == SR_PLUS_TIMES) {
+            for (int d = kWave / 2; d; d >>= 1) sum += __shfl_xor(sum, d);
+            if (lane == 0) atomicAdd(&reinterpret_cast<double*>(spa)[row], sum);
+        } else {
+            for (int d = kWave / 2; d; d >>= 1) {
+                const uint32_t o = __shfl_xor(acc, d);
+                if constexpr (SR == SR_MIN_SELECT2ND) acc = (uint32_t)min((int)acc, (int)o);
+                else acc |= o;
+            }
+            if (lane == 0) {
+                accumulate<SR>(&spa[row], acc);
+                atomicOr(&bm[row >> 5], 1u << (row & 31u));
+            }
+        }
+    }
+};
+
+// The most frequent of kTry rows sampled from a wave's K * 64 entries, as
+// count << 16 | row (rows < 2^15), for a maximum over waves.
+template <int K>
+__device__ __forceinline__ uint32_t frequent_row(const uint32_t (&r)[K], const bool (&ok)[K]) {
+    constexpr int kTry = 4;
+    uint32_t best = 0;
+    const int wid = threadIdx.x / kWave;
+#pragma unroll
+    for (int c = 0; c < kTry; ++c) {
+        const uint32_t cand = __builtin_amdgcn_readlane(r[c % K], (c * kWave / kTry + wid) & (kWave - 1));
+        int n = 0;
+#pragma unroll
+        for (int u = 0; u < K; ++u) n += __popcll(__ballot(ok[u] && r[u] == cand));
+        if (n) best = max(best, (uint32_t)n << 16 | cand);
+    }
+    return best;
+}
+
 // Bitmap bits of the fp64 cells a plus-times entry reached (cell no longer
-// -0.0), 64 consecutive cells per wave and step: conflict-free 8-byte LDS
-// reads, one ballot, and lane 0 merges the two bitmap words (nothing else
-// writes them after the accumulation).
+// -0.0): a wave reads kTouched runs of 64 consecutive cells (conflict-free
+// 8-byte LDS reads, all in flight together), lane s keeps the ballot of run s,
+// and each writes its two bitmap words at the end (nothing else writes them
+// after the accumulation).  With a read-modify-write of the bitmap per run
+// the pass over a 16384-row tile took 6 us, so 1.
+constexpr int kTouched = 8;
 template <int BLOCK>
 __device__ __forceinline__ void touched_bits64(const uint32_t* spa, uint32_t* bm, int rows) {
     const uint64_t* c64 = reinterpret_cast<const uint64_t*>(spa);
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = threadIdx.x / kWave;
-    for (int c0 = wid * kWave; c0 < rows; c0 += BLOCK) {
-        const int c = c0 + lane;
-        const bool t = c < rows && c64[c] != kNegZero64;
-        const uint64_t b = __ballot(t);
-        if (lane == 0) {
-            const int w = c0 >> 5;
-            bm[w] |= (uint32_t)b;
-            if (c0 + 32 < rows) bm[w + 1] |= (uint32_t)(b >> 32);
+    for (int c0 = wid * kTouched * kWave; c0 < rows; c0 += BLOCK * kTouched) {
+        uint64_t cell[kTouched], mine = 0;
+#pragma unroll
+        for (int s = 0; s < kTouched; ++s) cell[s] = c64[min(c0 + s * kWave + lane, rows - 1)];
+#pragma unroll
+        for (int s = 0; s < kTouched; ++s) {
+            const uint64_t b = __ballot(cell[s] != kNegZero64 && c0 + s * kWave + lane < rows);
+            mine = lane == s ? b : mine;
+        }
+        const int c = c0 + lane * kWave;   // first row of this lane's run
+        if (lane < kTouched && c < rows) {
+            bm[c >> 5] |= (uint32_t)mine;
+            if (c + 32 < rows) bm[(c >> 5) + 1] |= (uint32_t)(mine >> 32);
         }
     }
 }

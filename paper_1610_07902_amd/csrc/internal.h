@@ -473,6 +473,11 @@ constexpr int kTileLog2Wide = 14;  // widest plus-times tile (2^14 rows of 8-byt
 __host__ __device__ inline int merge_list_cap(int tile_log2, bool wide) {
     return tile_log2 + (wide ? 3 : 2) <= 16 ? (1 << tile_log2) : kMergeList;
 }
+// Rows k_merge lists at once: as above, but 64 KB of cells leave room for a
+// second workgroup on the compute unit (160 KB of LDS).
+__host__ __device__ inline int merge_list_rows(int tile_log2, bool wide) {
+    return tile_log2 + (wide ? 3 : 2) == 16 ? 7168 : merge_list_cap(tile_log2, wide);
+}
 // Tile of a call: plus-times merges in fp64 cells, so at most 2^14 rows.
 __host__ __device__ inline int tile_for(int tile_log2, int semiring) {
     return semiring == SR_PLUS_TIMES && tile_log2 > kTileLog2Wide ? kTileLog2Wide : tile_log2;

@@ -634,20 +634,35 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
 
 // ---------------------------------------------------------------- steps (c, d)
 // One workgroup per bucket.  The bucket's rows [row0, row0 + T) get an LDS
-// sparse accumulator (T values) and a T-bit touched bitmap.  The whole tile
-// is initialised while the bucket's first entries are in flight (a store
-// per row is far cheaper here than tracking first touches row by row);
-// every entry then updates its row as described above, and the number of
+// sparse accumulator (T values) and a T-bit touched bitmap; the number of
 // unique rows of Algorithm 1 step 2 is the population count of the bitmap.
 // The unique count joins a decoupled look-back across buckets to give the
-// bucket's offset in y (Algorithm 1, step 3) and the bitmap is walked in
-// order, so y comes out ascending; the walk compacts rows through a small
-// LDS list for coalesced y writes.
+// bucket's offset in y (Algorithm 1, step 3) and the rows go through an LDS
+// list in order, so y comes out ascending and its writes are coalesced.
+//
+// Two ways through the values:
+//   small: every entry in registers (BLOCK * ITEMS).  Each marks its row and
+//     clears that row's cell, so the tile is never initialised as a whole
+//     (1.7 us for 128 KB); the count is published before the adds, which then
+//     overlap the look-back's round trips of the buckets behind.
+//   long: the whole tile is initialised while the first entries are in flight,
+//     the next entries are loaded while one step's are added, and the row that
+//     a sample shows most often is summed in registers (HubSum).
+// Scale-22 R-MAT, one of 256 buckets per compute unit: with 5,500 entries per
+// bucket 15.4 us before, 10.3 now (launch and first loads 2.4, rows 1.2, count
+// and adds 1.9, look-back 2.4, writes 0.6); with 50,500 entries 39 before, 33
+// now.  The LDS bounds the latter: its fp64 adds retire 2 lanes per cycle, 10.5
+// us for the mean bucket and 14 for the longest; without hub sums 43 (one row
+// of the longest bucket has 16,000 of its 67,000 entries), with two rows in
+// registers instead of one 43 as well (conversions and adds of every entry).
 //
 // Batched calls (BATCH): workgroup k merges key k = vector * nbx + bucket;
 // the look-back runs over all keys, so y holds the vectors' results one
 // after another (each ascending) and the first bucket of each vector
-// publishes where its part starts (yoff).
+// publishes where its part starts (yoff).  Most keys of a batch are short and
+// wait behind long ones, so two workgroups share a compute unit: four entries
+// per thread (at most 64 registers) and the shorter list of merge_list_rows.
+// 64 vectors on a scale-20 graph: 302 us before, 245 now.
 __device__ __forceinline__ void publish_total(const MergeArgs& a, int64_t total, bool batch) {
     a.ctrl->nnz_y = total;
     if (a.d_nnz_y) *a.d_nnz_y = total;
@@ -656,15 +671,17 @@ __device__ __forceinline__ void publish_total(const MergeArgs& a, int64_t total,
     if (batch) a.yoff[a.nbatch] = total;
 }
 
+constexpr uint32_t kHubMin = 16;   // of a wave's sampled entries: fewer cost less in the cells than in registers
+
 template <int BLOCK, int ITEMS, int SR, bool BFS, bool BATCH>
-__global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
+__global__ __launch_bounds__(BLOCK, BATCH ? 8 : 1) void k_merge(MergeArgs a) {
     extern __shared__ __align__(16) uint32_t lds_merge[];
     const int tl = a.tile_log2;
     const int T = 1 << tl;
     constexpr bool kWide = SR == SR_PLUS_TIMES;                      // fp64 cells
     uint32_t* spa = lds_merge;                                       // [T] cells of 4 or 8 bytes
     uint32_t* bm = spa + (kWide ? 2 * T : T);                        // [T/32]
-    uint16_t* list = reinterpret_cast<uint16_t*>(bm + (T >> 5));     // [merge_list_cap(tl, kWide)]
+    uint16_t* list = reinterpret_cast<uint16_t*>(bm + (T >> 5));     // [merge_list_rows(tl, kWide)]
     __shared__ int64_t s_excl;
     __shared__ int s_tmp[BLOCK / kWave + 1];
     const int tid = threadIdx.x;
@@ -715,19 +732,22 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
     const int cnt = min(cnt_raw, cap);
     const int nw = (rows + 31) >> 5;
     const bool small = cnt <= BLOCK * ITEMS;
-    const bool sparse = cnt < rows / 8;   // plus-times: mark rows per entry, skip the ballot pass
-    uint32_t rr[ITEMS], vv[ITEMS];
-    if (small) {   // the whole bucket in registers: issue every load before the tile set-up
+    // The first ITEMS entries per thread (all of a small bucket's), issued
+    // before the tile set-up; indices clamped, so every load is unconditional.
+    uint2 ent[ITEMS];
+    auto load_entries = [&](int e0) {
+        if (cnt == 0) return;   // only after an overflow: no slot to read
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
-            const int e = i * BLOCK + tid;
-            const uint2 ent = a.buckets[base + (e < cnt ? e : 0)];
-            rr[i] = e < cnt ? ent.x : 0xffffffffu;
-            vv[i] = ent.y;
+            const int e = e0 + i * BLOCK + tid;
+            ent[i] = a.buckets[base + (e < cnt ? e : 0)];
         }
-    }
+    };
+    load_entries(0);
+    __shared__ uint32_t s_hub;
+    if (tid == 0) s_hub = 0u;
     for (int w = tid; w < nw; w += BLOCK) bm[w] = 0u;
-    {
+    if (!small) {
         // whole bitmap words of cells, 16 bytes per store
         uint4* spa4 = reinterpret_cast<uint4*>(spa);
         if constexpr (kWide) {
@@ -740,54 +760,78 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
     }
     __syncthreads();
     bool bad = false;
-    if (small) {
-        bool ok[ITEMS];
+    uint32_t rr[ITEMS], vv[ITEMS];
+    bool ok[ITEMS];
+    auto take_entries = [&](int e0) {
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
-            ok[i] = rr[i] != 0xffffffffu;
-            rr[i] -= (uint32_t)row0;
+            rr[i] = ent[i].x - (uint32_t)row0;
+            vv[i] = ent[i].y;
+            ok[i] = e0 + i * BLOCK + tid < cnt;
             if (ok[i] && rr[i] >= (uint32_t)rows) {   // unwritten slot after an overflow
                 ok[i] = false;
                 bad = true;
             }
         }
-        add_rows<SR, ITEMS>(rr, vv, ok, spa, bm, sparse);
+    };
+    if (small) {
+        // every entry marks its row and clears the row's cell
+        take_entries(0);
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            if (!ok[i]) continue;
+            atomicOr(&bm[rr[i] >> 5], 1u << (rr[i] & 31u));
+            if constexpr (kWide) reinterpret_cast<uint64_t*>(spa)[rr[i]] = kNegZero64;
+            else spa[rr[i]] = identity<SR>();
+        }
     } else {
-        constexpr int kBatch = 8;   // entries per thread in flight per step
-        for (int e0 = 0; e0 < cnt; e0 += BLOCK * kBatch) {
-            uint2 ent[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int e = e0 + u * BLOCK + tid;
-                ent[u] = e < cnt ? a.buckets[base + e] : make_uint2(0xffffffffu, 0u);
-            }
-            uint32_t r[kBatch], v[kBatch];
-            bool ok[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                r[u] = ent[u].x - (uint32_t)row0;
-                v[u] = ent[u].y;
-                ok[u] = e0 + u * BLOCK + tid < cnt;
-                if (ok[u] && r[u] >= (uint32_t)rows) {
-                    ok[u] = false;
-                    bad = true;
-                }
-            }
-            add_rows<SR, kBatch>(r, v, ok, spa, bm, sparse);
+        HubSum<SR> hub;
+        take_entries(0);
+        const uint32_t freq = frequent_row<ITEMS>(rr, ok);
+        if ((tid & (kWave - 1)) == 0 && freq >> 16 >= kHubMin) atomicMax(&s_hub, freq);
+        __syncthreads();
+        if (s_hub) hub.row = s_hub & 0xffffu;
+        // The next entries are on their way while these are added.
+        for (int e0 = 0; e0 < cnt; e0 += BLOCK * ITEMS) {
+            if (e0) take_entries(e0);
+            load_entries(e0 + BLOCK * ITEMS);
+            hub.take(rr, vv, ok);
+            add_rows<SR, ITEMS>(rr, vv, ok, spa, bm);
+        }
+        hub.flush(spa, bm);
+        if (kWide) {
+            __syncthreads();
+            touched_bits64<BLOCK>(spa, bm, rows);
         }
     }
-    if (bad) raise_err(&a.ctrl->err, ERR_BUCKET_OVERFLOW, a.rep);
     __syncthreads();
-    if (kWide && !sparse) {
-        touched_bits64<BLOCK>(spa, bm, rows);
-        __syncthreads();
+    // Unique rows, 16 per thread and step, listed in order while the list
+    // holds them; the count goes out before a small bucket's values are
+    // added, so the look-backs behind this one overlap them.
+    auto list_rows = [&](uint32_t bits, int r0, int at) {
+        while (bits) {
+            list[at++] = (uint16_t)(r0 + __ffs(bits) - 1);
+            bits &= bits - 1u;
+        }
+    };
+    const int cap_list = merge_list_rows(tl, kWide);
+    int ucnt = 0, pos = 0;
+    uint32_t half = 0;
+    for (int h0 = 0; h0 < 2 * nw; h0 += BLOCK) {
+        const int h = h0 + tid;
+        half = h < 2 * nw ? (bm[h >> 1] >> (16 * (h & 1))) & 0xffffu : 0u;
+        int tot;
+        pos = ucnt + block_exclusive_i32<BLOCK>(__popc(half), s_tmp, tot);
+        ucnt += tot;
+        if (h0 + BLOCK < 2 * nw && ucnt <= cap_list) list_rows(half, h << 4, pos);   // the last step below
     }
-    int pc = 0;
-    for (int w = tid; w < nw; w += BLOCK) pc += __popc(bm[w]);
-    int ucnt;
-    (void)block_exclusive_i32<BLOCK>(pc, s_tmp, ucnt);
+    if (tid == 0) publish_sum(a.lb3, b, (uint64_t)ucnt);
+    if (small) add_values<SR, ITEMS>(rr, vv, ok, spa);
+    const bool listed = ucnt <= cap_list;
+    if (listed) list_rows(half, ((2 * nw - 1) / BLOCK * BLOCK + tid) << 4, pos);
+    if (bad) raise_err(&a.ctrl->err, ERR_BUCKET_OVERFLOW, a.rep);
     if (tid < kWave) {
-        const uint64_t e = lookback(a.lb3, b, (uint64_t)ucnt, &a.ctrl->err, a.rep);
+        const uint64_t e = lookback<4>(a.lb3, b, (uint64_t)ucnt, &a.ctrl->err, a.rep);
         if (tid == 0) {
             s_excl = (int64_t)e;
             if (BATCH && bt == 0) a.yoff[xb] = (int64_t)e;
@@ -806,44 +850,62 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
         visited += (int64_t)xb * a.mask_words;
     }
 
-    // In-order walk of the bitmap: one word per thread per round, as many
-    // words as the LDS list holds (the whole tile up to 16K rows).
-    const int round_words = min(BLOCK, merge_list_cap(tl, kWide) >> 5);
-    int64_t carry = 0;
-    for (int w0 = 0; w0 < nw; w0 += round_words) {
-        const int w = w0 + tid;
-        const bool mine = tid < round_words && w < nw;
-        const uint32_t bits = mine ? bm[w] : 0u;
-        if (!BFS && !BATCH && a.y_bits && mine) a.y_bits[(row0 >> 5) + w] = bits;
-        int tot;
-        const int pos = block_exclusive_i32<BLOCK>(__popc(bits), s_tmp, tot);
-        if (BFS && bits) visited[(row0 >> 5) + w] |= bits;
-        uint32_t rest = bits;
-        int k = 0;
-        while (rest) {
-            const int bitpos = __ffs(rest) - 1;
-            rest &= rest - 1u;
-            list[pos + k] = (uint16_t)((w << 5) + bitpos);
-            ++k;
-        }
-        __syncthreads();
-        for (int t = tid; t < tot; t += BLOCK) {
-            const int r = list[t];
-            const int64_t o = excl + carry + t;
-            uint32_t v;
-            if constexpr (kWide) v = __float_as_uint((float)reinterpret_cast<const double*>(spa)[r]);
-            else v = spa[r];
-            if (o < a.y_cap) {
-                a.y_idx[o] = row0 + r;
-                if (a.y_val) store_value<SR>(a.y_val, o, v);
+    // `tot` listed rows to y from position o0, kOut per thread in flight
+    auto write_rows = [&](int64_t o0, int tot) {
+        constexpr int kOut = 4;
+        for (int t0 = 0; t0 < tot; t0 += kOut * BLOCK) {
+            int r[kOut];
+            uint32_t v[kOut];
+#pragma unroll
+            for (int u = 0; u < kOut; ++u) r[u] = list[min(t0 + u * BLOCK + tid, tot - 1)];
+#pragma unroll
+            for (int u = 0; u < kOut; ++u) {
+                if constexpr (kWide) v[u] = __float_as_uint((float)reinterpret_cast<const double*>(spa)[r[u]]);
+                else v[u] = spa[r[u]];
             }
-            if (BFS) {
-                level[row0 + r] = lvl;
-                if (parent) parent[row0 + r] = (int32_t)v;
+#pragma unroll
+            for (int u = 0; u < kOut; ++u) {
+                const int t = t0 + u * BLOCK + tid;
+                if (t >= tot) continue;
+                const int64_t o = o0 + t;
+                if (o < a.y_cap) {
+                    a.y_idx[o] = row0 + r[u];
+                    if (a.y_val) store_value<SR>(a.y_val, o, v[u]);
+                }
+                if (BFS) {
+                    level[row0 + r[u]] = lvl;
+                    if (parent) parent[row0 + r[u]] = (int32_t)v[u];
+                }
             }
         }
-        carry += tot;
-        __syncthreads();
+    };
+    if (!BATCH && (BFS || a.y_bits))
+        for (int w = tid; w < nw; w += BLOCK) {
+            const uint32_t bits = bm[w];
+            if (!BFS) a.y_bits[(row0 >> 5) + w] = bits;
+            else if (bits) visited[(row0 >> 5) + w] |= bits;
+        }
+    if (BATCH && BFS)
+        for (int w = tid; w < nw; w += BLOCK)
+            if (const uint32_t bits = bm[w]) visited[(row0 >> 5) + w] |= bits;
+    if (listed) {
+        write_rows(excl, ucnt);
+    } else {
+        // In-order walk of the bitmap: one word per thread per round, as many
+        // words as the LDS list holds.
+        const int round_words = min(BLOCK, cap_list >> 5);
+        int64_t carry = 0;
+        for (int w0 = 0; w0 < nw; w0 += round_words) {
+            const int w = w0 + tid;
+            const uint32_t bits = tid < round_words && w < nw ? bm[w] : 0u;
+            int tot;
+            const int at = block_exclusive_i32<BLOCK>(__popc(bits), s_tmp, tot);
+            list_rows(bits, w << 5, at);
+            __syncthreads();
+            write_rows(excl + carry, tot);
+            carry += tot;
+            __syncthreads();
+        }
     }
     if (!BATCH && b == 0 && a.stat) collect_stats<BLOCK>(a);
 }
@@ -853,7 +915,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(MergeArgs a) {
 size_t merge_lds_bytes(int tile_log2, int semiring) {
     const bool wide = semiring == SR_PLUS_TIMES;
     const size_t T = size_t(1) << tile_log2;
-    return T * (wide ? 8 : 4) + (T / 32) * 4 + size_t(merge_list_cap(tile_log2, wide)) * 2;
+    return T * (wide ? 8 : 4) + (T / 32) * 4 + size_t(merge_list_rows(tile_log2, wide)) * 2;
 }
 
 size_t scatter_lds_bytes(int nb, int chunk, bool batch) {
@@ -1032,7 +1094,7 @@ hipError_t launch_scatter_batch(const ScatterArgs& a, int semiring, int block, i
 template <int BLOCK, int SR, bool BFS, bool BATCH>
 static hipError_t merge_one(const MergeArgs& a, hipStream_t s, const LaunchEvents* ev) {
     const size_t lds = merge_lds_bytes(a.tile_log2, SR);
-    auto kern = k_merge<BLOCK, kMergeItems, SR, BFS, BATCH>;
+    auto kern = k_merge<BLOCK, BATCH ? kMergeItems / 2 : kMergeItems, SR, BFS, BATCH>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     launch_k(kern, dim3(a.nb), dim3(BLOCK), lds, s, ev, a);
