@@ -1,5 +1,5 @@
 // Direction (and selector class) of a BFS level, shared by the decision
-// kernels (k_decide, k_select) and by the scan, which takes the decision
+// kernel k_select and by the scan, which takes the heuristic's, and either's
 // itself when the previous level ran pull and its emit left the new
 // frontier's column sums behind.  Not installed.
 #pragma once

@@ -126,12 +126,12 @@ struct ScanArgs {
     int wide;                // 1: tiles of kScanItemsWide items per thread (large or device-known f)
     // Direction-switching BFS with the pull direction: 1 heuristic, 2
     // selector (weights in sel), 0 otherwise.  After a pull level the scan
-    // decides the direction itself and builds no tables for a pull level; on
-    // a push level it clears the x bits that pull level left.
+    // decides the direction from that level's sums and builds no tables for a
+    // pull level; else its last tile takes the heuristic's decision.
     int chain;
     const float* sel;
     int has_pull;
-    uint32_t* xbits;
+    uint64_t* chain_lbp;         // [chain_nparts] the emit's look-back words
     const int64_t* chain_part;   // [2 * chain_nparts] the previous emit's per-workgroup column sums
     int32_t chain_nparts;
     // Batched calls: x is the concatenation of nbatch vectors, vector b at
@@ -259,8 +259,9 @@ struct MergeArgs {
     const ExpandStat* stat;
     int32_t stat_n;
     int64_t nnz;             // more products than stored entries mean repeated x indices
-    // bitvector output (single calls, not BFS or batched): every word of y's
-    // bitmap is written from the tiles' touched-row bitmaps; nullable
+    // bitvector output (not batched) and next frontier of a direction-switching
+    // BFS: every word of y's bitmap is written from the tiles' touched-row
+    // bitmaps; nullable
     uint32_t* y_bits;
 };
 // Merge variant 1: rows per output tile of the in-order walk.
@@ -303,7 +304,7 @@ struct PullArgs {
     int gate;                // 1: skip when ctrl->dir selects push
     // BFS level of a direction-switching BFS: the emit writes the next
     // frontier's bitmap over xbits and sums its column lengths (colptr) for
-    // the next decision; prep leaves xbits as the previous emit wrote them.
+    // the next decision; there is no prep: the previous level wrote xbits.
     int chain;
     const int32_t* colptr;
     int64_t* chain_part;     // [2 * emit_blocks]: per workgroup, stored entries and (longest << 32 | non-empty)
@@ -574,7 +575,6 @@ hipError_t launch_validate_jc(const int32_t* jc, int32_t nzc, int32_t n, Ctrl* c
 int64_t bits_tiles(int64_t n);
 hipError_t launch_bits_to_list(const uint32_t* bits, int32_t n, int32_t* out, int32_t* count, int32_t* tile_counts,
                                Ctrl* ctrl, hipStream_t s);
-hipError_t launch_decide(Ctrl* ctrl, int32_t n, int64_t nnz, hipStream_t s);
 hipError_t launch_pr_init(int32_t n, const int32_t* colptr, float d, float* rank, int32_t* x_idx, float* x_val,
                           Ctrl* ctrl, hipStream_t s);
 hipError_t launch_pr_update(int32_t n, const int32_t* colptr, float d, float tol, float* rank, const int32_t* y_idx,

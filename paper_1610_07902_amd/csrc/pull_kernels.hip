@@ -7,23 +7,19 @@
 // (Conclusions).  Rows are read in CSR form: the transpose built at create,
 // or A itself when the caller declares A symmetric.
 //
-// Three launches: k_pull_prep scatters x into a bitmap + dense values;
+// Three launches (two in a direction-switching BFS, where the kernel before
+// left x's bitmap): k_pull_prep scatters x into a bitmap + dense values;
 // k_pull walks a merge-path partition of (row ends + stored entries) so every
 // workgroup gets the same number of steps whatever the row lengths; k_emit
 // walks the result bitmap in order (decoupled look-back across workgroups),
 // writes y ascending and restores the zeroed / identity state of the dense
 // buffers for the next call.
 
-#include "internal.h"
+#include "device_ops.h"
 
 namespace spv {
 
 namespace {
-
-constexpr uint64_t LBP_AGG = 1ull << 62;
-constexpr uint64_t LBP_INC = 2ull << 62;
-constexpr uint64_t LBP_VAL = (1ull << 62) - 1;
-constexpr int kSpinMaxP = 1 << 20;
 
 __device__ __forceinline__ int32_t ldc(const int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -60,14 +56,10 @@ __device__ __forceinline__ void comb_global(uint32_t* cell, uint32_t v) {
 // ---------------------------------------------------------------- x -> dense
 template <int XMODE>
 __global__ __launch_bounds__(256) void k_pull_prep(PullArgs a) {
-    if (a.gate && ldc(&a.ctrl->dir) != 1) return;   // this BFS level runs push
     const int f = a.f_dev ? ldc(a.f_dev) : a.f_host;
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.bump_level && f > 0) stc(&a.ctrl->level, ldc(&a.ctrl->level) + 1);
     // the emit look-back words of this call (the previous emit has finished)
     for (int i = blockIdx.x * 256 + threadIdx.x; i < a.emit_blocks; i += gridDim.x * 256) a.lbp[i] = 0;
-    // after a pull level the x bitmap already holds this frontier (its emit
-    // wrote it); the BFS pull reads vertex ids, not xdense
-    if (a.chain && __hip_atomic_load(&a.ctrl->chain_ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
     // Bitmap words are ORed once per run of lanes sharing a word (a sorted
     // frontier puts up to 32 consecutive lanes on one word, whose atomics
     // would otherwise serialise on one address).
@@ -388,43 +380,12 @@ __global__ __launch_bounds__(256) void k_pull_bfs(PullArgs a) {
 // call and clears the x bits this call set; in a direction-switching BFS it
 // writes the new frontier over the x bits instead and leaves per-workgroup
 // sums of its column lengths for the next level's decision.
+// Bound by the gathers per listed row (column ends, value) and its scattered
+// stores: one bitmap word per thread and four rows in flight each.  With 1024
+// words per workgroup a scale-22 graph had 128 workgroups of four waves and a
+// level of 1.6 million rows took 56.6 us; with 256 words, 26.0.
 constexpr int kEmitBlock = 256;
-constexpr int kEmitWords = 1024;
-
-__device__ uint64_t lookback_p(uint64_t* st, int tile, uint64_t agg, uint32_t* err) {
-    const int lane = threadIdx.x & 63;
-    if (tile == 0) {
-        if (lane == 0) __hip_atomic_store(&st[0], LBP_INC | agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return 0;
-    }
-    if (lane == 0) __hip_atomic_store(&st[tile], LBP_AGG | agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint64_t excl = 0;
-    int base = tile - 1, spins = 0;
-    for (;;) {
-        const int idx = base - lane;
-        const uint64_t w = idx >= 0 ? __hip_atomic_load(&st[idx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : LBP_INC;
-        const uint64_t status = w >> 62;
-        const uint64_t inc = __ballot(status == 2), emp = __ballot(status == 0);
-        const uint64_t need = inc ? (((inc & (~inc + 1)) << 1) - 1) : ~0ull;
-        if (emp & need) {
-            if (++spins > kSpinMaxP) {
-                if (lane == 0) atomicOr(err, ERR_SPIN);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-            continue;
-        }
-        uint64_t v = ((need >> lane) & 1ull) ? (w & LBP_VAL) : 0ull;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-        excl += v;
-        if (inc) break;
-        base -= 64;
-    }
-    if (lane == 0) __hip_atomic_store(&st[tile], LBP_INC | ((excl + agg) & LBP_VAL), __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_AGENT);
-    return excl;
-}
+constexpr int kEmitWords = 256;
 
 template <int SR, bool BFS>
 __global__ __launch_bounds__(kEmitBlock) void k_emit(PullArgs a) {
@@ -478,7 +439,7 @@ __global__ __launch_bounds__(kEmitBlock) void k_emit(PullArgs a) {
     const int pos = s_tmp[wid] + x - cnt;
     const int tot = s_tmp[kEmitBlock / 64];
     if (tid < 64) {
-        const uint64_t e = lookback_p(a.lbp, blockIdx.x, (uint64_t)tot, &a.ctrl->err);
+        const uint64_t e = lookback<4>(a.lbp, blockIdx.x, (uint64_t)tot, &a.ctrl->err);
         if (tid == 0) {
             s_excl = (int64_t)e;
             if (blockIdx.x == gridDim.x - 1) {
@@ -515,27 +476,37 @@ __global__ __launch_bounds__(kEmitBlock) void k_emit(PullArgs a) {
     __syncthreads();
     int64_t csum = 0;   // chain: column lengths of this workgroup's new frontier vertices
     int cmax = 0, cnz = 0;
-    for (int t = tid; t < tot; t += kEmitBlock) {
-        const int r = (w0 << 5) + s_list[t];
+    constexpr int kOut = 4;
+    for (int t0 = tid; t0 < tot; t0 += kOut * kEmitBlock) {
+        int r[kOut], d[kOut];
+        uint32_t v[kOut];
+#pragma unroll
+        for (int u = 0; u < kOut; ++u) r[u] = (w0 << 5) + s_list[min(t0 + u * kEmitBlock, tot - 1)];
+#pragma unroll
+        for (int u = 0; u < kOut; ++u) v[u] = a.ydense[r[u]];
         if (a.chain) {
-            const int d = a.colptr[r + 1] - a.colptr[r];
-            csum += d;
-            cmax = max(cmax, d);
-            cnz += d > 0 ? 1 : 0;
+#pragma unroll
+            for (int u = 0; u < kOut; ++u) d[u] = a.colptr[r[u] + 1] - a.colptr[r[u]];
         }
-        const uint32_t v = a.ydense[r];
-        a.ydense[r] = ident<SR>();
-        const int64_t o = excl + t;
-        if (o < a.y_cap) {
-            a.y_idx[o] = r;
-            if (a.y_val) {
-                if (SR == SR_OR_AND) reinterpret_cast<uint8_t*>(a.y_val)[o] = (uint8_t)(v != 0u);
-                else reinterpret_cast<uint32_t*>(a.y_val)[o] = v;
+#pragma unroll
+        for (int u = 0; u < kOut; ++u) {
+            const int t = t0 + u * kEmitBlock;
+            if (t >= tot) break;
+            if (a.chain) {
+                csum += d[u];
+                cmax = max(cmax, d[u]);
+                cnz += d[u] > 0 ? 1 : 0;
             }
-        }
-        if (BFS) {
-            level[r] = lvl;
-            if (parent) parent[r] = (int32_t)v;
+            a.ydense[r[u]] = ident<SR>();
+            const int64_t o = excl + t;
+            if (o < a.y_cap) {
+                a.y_idx[o] = r[u];
+                if (a.y_val) store_value<SR>(a.y_val, o, v[u]);
+            }
+            if (BFS) {
+                level[r[u]] = lvl;
+                if (parent) parent[r[u]] = (int32_t)v[u];
+            }
         }
     }
     if (a.chain) {   // this workgroup's sums, read by the next level's scan (a later kernel)
@@ -564,7 +535,7 @@ __global__ __launch_bounds__(kEmitBlock) void k_emit(PullArgs a) {
             if (blockIdx.x == 0) __hip_atomic_store(&a.ctrl->chain_ready, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    // the look-back words of this call are cleared by the next k_pull_prep
+    // the look-back words of this call are cleared by the next k_pull_prep (or k_scan)
 }
 
 __global__ void k_lbp_clear(uint64_t* lbp, int n) {
@@ -623,7 +594,10 @@ hipError_t launch_pull(const PullArgs& a, int semiring, int xmode, bool bfs, boo
     int64_t fg = (a.f_host + 255) / 256 + 1;
     if (a.f_dev || fg > 512) fg = 512;
     const int f_grid = (int)fg;
-    switch (xmode) {
+    // A level of a direction-switching BFS finds its frontier in the x bitmap
+    // already (the merge or the emit before it wrote every word; the BFS pull
+    // reads vertex ids, not xdense), and its scan cleared the look-back words.
+    if (!a.chain) switch (xmode) {
         case XV_BITS32: hipLaunchKernelGGL(k_pull_prep<XV_BITS32>, dim3(f_grid), dim3(256), 0, s, a); break;
         case XV_INDEX: hipLaunchKernelGGL(k_pull_prep<XV_INDEX>, dim3(f_grid), dim3(256), 0, s, a); break;
         case XV_U8: hipLaunchKernelGGL(k_pull_prep<XV_U8>, dim3(f_grid), dim3(256), 0, s, a); break;

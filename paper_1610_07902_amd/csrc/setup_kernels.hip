@@ -1,7 +1,7 @@
 // Set-up kernels: run once per matrix (spmspv_create) or once per BFS.
 // Not on the per-multiply path.
 
-#include "decide.h"
+#include "internal.h"
 
 namespace spv {
 
@@ -114,7 +114,9 @@ __global__ void k_bfs_init(int32_t n, int32_t root, int32_t* level, int32_t* par
     const int64_t nw = ((int64_t)n + 31) >> 5;
     for (int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; w < nw; w += stride) {
         visited[w] = (w == (root >> 5)) ? (1u << (root & 31)) : 0u;
-        if (xbits) xbits[w] = 0u;   // a BFS that stopped early may have left a pull frontier there
+        // the first frontier of a direction-switching search (policy); a search
+        // that stopped early may have left another one there
+        if (xbits) xbits[w] = policy && w == (root >> 5) ? 1u << (root & 31) : 0u;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         ctrl->chain_ready = 0;
@@ -194,16 +196,6 @@ __global__ void k_gen_x(int32_t n, uint64_t thresh, uint64_t seed, int32_t* x_id
     }
 }
 
-// Direction of the next BFS level from the frontier just scanned (the
-// frontier-edge rule of heuristic_step), unless the scan of this level
-// already took the decision.
-__global__ void k_decide(Ctrl* ctrl, int32_t n, int64_t nnz) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    if (consume_chain(ctrl)) return;
-    heuristic_step(ctrl, n, dc_ld(&ctrl->f), dc_ld(&ctrl->W));
-    (void)nnz;
-}
-
 inline int grid_for(int64_t count, int block, int cap = 4096) {
     int64_t g = (count + block - 1) / block;
     if (g < 1) g = 1;
@@ -255,11 +247,6 @@ hipError_t launch_validate_colptr(const int32_t* colptr, int32_t n, int64_t nnz,
                                  hipStream_t s) {
     hipLaunchKernelGGL(k_validate_colptr, dim3(grid_for(n, kSetupBlock)), dim3(kSetupBlock), 0, s, colptr, n, nnz,
                        ctrl, maxout);
-    return hipGetLastError();
-}
-
-hipError_t launch_decide(Ctrl* ctrl, int32_t n, int64_t nnz, hipStream_t s) {
-    hipLaunchKernelGGL(k_decide, dim3(1), dim3(64), 0, s, ctrl, n, nnz);
     return hipGetLastError();
 }
 

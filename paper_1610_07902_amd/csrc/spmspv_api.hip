@@ -58,7 +58,7 @@ inline int ceil_log2(int64_t v) {
 // Offsets of every region inside the caller's workspace.
 struct Layout {
     size_t ctrl, rcp, partials, cstart, coff, cxv, chunk_col, lb1, cursor, lb3, xw, xrec, buckets, visited, front0,
-        front1, front2, pmin, bar, samples, gpoff, roff, gb_lb, gb_bytes, bv_idx, bv_val, bv_tiles, dc_aux, det_list,
+        front1, front2, pmin, samples, gpoff, roff, gb_lb, gb_bytes, bv_idx, bv_val, bv_tiles, dc_aux, det_list,
         det_counts, det_partials, det_long, det_long_count, h_f64, h_i32, h_orbits, h_touched, total;
     // pull direction (present with SPMSPV_WITH_TRANSPOSE or SPMSPV_SYMMETRIC)
     size_t p_xbits, p_xdense, p_ybits, p_ydense, p_lbp, p_part, p_chain, t_colids, t_values, selector;
@@ -114,7 +114,6 @@ Layout make_layout(int64_t m, int64_t n, int64_t nnz, int flags = 0, int64_t dc_
     L.front1 = take(size_t(m) * 4);
     L.front2 = take(size_t(m) * 4);
     L.pmin = take(size_t(m) * 4);
-    L.bar = take(kPersistBarWords * 4);
     L.selector = take(size_t(kMlpParams + 2 * kMlpIn) * 4);
     // one-launch multiply: list samples, source prefix and per-chunk bucket offsets
     L.samples = take(size_t(kFMaxGrid) * kFSamples * 4);
@@ -567,7 +566,7 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
         sa.chain = learned_gate ? 2 : 1;
         sa.sel = A->selector;
         sa.has_pull = 1;
-        sa.xbits = A->p_xbits;
+        sa.chain_lbp = A->p_lbp;
         sa.chain_part = A->p_chain;
         sa.chain_nparts = pull_emit_blocks((int32_t)A->m);
     }
@@ -635,7 +634,8 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
     ma.h_orbits = reinterpret_cast<uint32_t*>(A->ws + A->L.h_orbits);
     ma.h_touched = reinterpret_cast<uint32_t*>(A->ws + A->L.h_touched);
     ma.h_split = std::max(1, std::min(1024, 4 * A->num_cu / nb));   // about four workgroups per CU
-    ma.y_bits = bfs ? nullptr : y_bits;
+    // a direction-switching level leaves the next frontier where a pull reads it
+    ma.y_bits = bfs ? (sa.chain ? A->p_xbits : nullptr) : y_bits;
     ma.rep = rep;
 
     // With profiling, each kernel's own start and end timestamps go to a pair
@@ -692,8 +692,6 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
         HIP_TRY(launch_scan(sa, (int)g1, s, ev ? &le[0] : nullptr));
         if (diropt && learned_gate)   // the selector picks the direction on the device
             HIP_TRY(launch_select(A->ctrl, A->selector, (int32_t)A->n, A->nnz, A->pull ? 1 : 0, 1, -1, s));
-        else if (diropt)
-            HIP_TRY(launch_decide(A->ctrl, (int32_t)A->n, A->nnz, s));
     }
     if (phases & 2)
         HIP_TRY(launch_scatter(ca, semiring, sc.scatter_block, sc.scatter_items, (int)g2, s, ev ? &le[1] : nullptr));
@@ -1205,7 +1203,9 @@ void bind_workspace(spmspv_matrix* A, int64_t m, int64_t n, int64_t nnz, const i
     A->front[1] = reinterpret_cast<int32_t*>(A->ws + L.front1);
     A->front2 = reinterpret_cast<int32_t*>(A->ws + L.front2);
     A->pmin = reinterpret_cast<int32_t*>(A->ws + L.pmin);
-    A->bar = reinterpret_cast<uint32_t*>(A->ws + L.bar);
+    // in the one-launch multiply's scratch: a search clears it before each launch
+    static_assert(kPersistBarWords <= kFMaxGrid * kFSamples, "barrier words");
+    A->bar = reinterpret_cast<uint32_t*>(A->ws + L.samples);
     A->selector = reinterpret_cast<float*>(A->ws + L.selector);
     A->bv_idx = reinterpret_cast<int32_t*>(A->ws + L.bv_idx);
     A->bv_val = reinterpret_cast<uint32_t*>(A->ws + L.bv_val);
@@ -1433,8 +1433,6 @@ int create_impl(spmspv_handle* h_out, int64_t m, int64_t n, int64_t nnz, int64_t
     if ((e = launch_exclusive_scan_i32(A->rcp, m + 1, reinterpret_cast<int32_t*>(A->ws + L.partials), s)) !=
         hipSuccess)
         return bail(hip_fail(e, "row count scan"));
-    if ((e = launch_fill_u32(A->bar, 0u, kPersistBarWords, s)) != hipSuccess)
-        return bail(hip_fail(e, "persistent BFS state"));
     // the HBM accumulator starts (and is left after every call) empty
     if ((e = reset_persistent_state(A, s)) != hipSuccess ||
         (e = launch_fill_u32(reinterpret_cast<uint32_t*>(A->ws + L.h_i32), 0x7fffffffu, L.h_rows, s)) != hipSuccess ||
@@ -1956,7 +1954,7 @@ int bfs_run(spmspv_handle A, int semiring, int32_t root, int flags, int32_t* lev
                              A->visited, st, nullptr, diropt, -1, 3, 0, learned_gate);
             if (rc) return rc;
             if (diropt) {
-                // pull kernels for the same level; they run only when k_decide chose pull
+                // pull kernels for the same level; they run only when the scan chose pull
                 rc = enqueue_pull(A, semiring, xmode, 0, &A->ctrl->f, x, nullptr, y, nullptr, A->m, nullptr, true,
                                   A->visited, false, true, st, nullptr);
                 if (rc) return rc;
@@ -2073,6 +2071,8 @@ int bfs_run(spmspv_handle A, int semiring, int32_t root, int flags, int32_t* lev
     }
     if (h.err) {
         clear_err(A, s);
+        if (diropt)   // a level that failed may have left its frontier there; other pulls find it zero
+            HIP_TRY(launch_fill_u32(A->p_xbits, 0u, (A->n + 31) / 32, s));
         return fail(SPMSPV_EDEVICE, "device error bits " + std::to_string(h.err));
     }
     if (h_num_levels) *h_num_levels = h.level;

@@ -95,11 +95,13 @@ __global__ __launch_bounds__(BLOCK) void k_scan(ScanArgs a) {
             st_ctrl(&a.ctrl->W, 0);
             st_ctrl(&a.ctrl->fnz, 0);
             a.coff[0] = 0;
+            if (CHAIN && a.chain == 1 && !chain_ready) heuristic_step(a.ctrl, a.n, f, 0);
         }
     }
     if (tid == 0) s_max = 0;
-    bool clear_x = false;   // push level after a pull level: clear the x bits that level left
     if constexpr (CHAIN) {
+        // the emit's look-back words, should this level run pull
+        for (int i = blockIdx.x * BLOCK + tid; i < a.chain_nparts; i += gridDim.x * BLOCK) a.chain_lbp[i] = 0;
         // Direction-switching BFS after a pull level: that level's emit left
         // per-workgroup sums of this frontier's column lengths, so the
         // decision is taken here (workgroup 0 adds them up and publishes the
@@ -169,7 +171,6 @@ __global__ __launch_bounds__(BLOCK) void k_scan(ScanArgs a) {
             }
             __syncthreads();
             if (s_dir) return;
-            clear_x = true;
         }
     }
     const int ntiles = (f + TILE - 1) / TILE;
@@ -188,11 +189,6 @@ __global__ __launch_bounds__(BLOCK) void k_scan(ScanArgs a) {
         // values) so every thread has all its gathers in flight at once.
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) jj[i] = (p0 + i < f) ? a.x_idx[p0 + i] : -1;
-        if (CHAIN && clear_x) {
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i)
-                if (jj[i] >= 0 && jj[i] < a.n) a.xbits[jj[i] >> 5] = 0u;
-        }
         bool bad = false;
         int32_t b0[ITEMS], b1[ITEMS];
         if (a.dcsc) {
@@ -287,7 +283,11 @@ __global__ __launch_bounds__(BLOCK) void k_scan(ScanArgs a) {
         }
         if (lost) atomicOr(&a.ctrl->err, ERR_SPIN);
         if (tile == ntiles - 1 && tid == BLOCK - 1) {
-            if (off > (uint64_t)a.nnz || c > (uint64_t)f) {
+            const bool over = off > (uint64_t)a.nnz || c > (uint64_t)f;
+            // the level's direction from the frontier just scanned, unless it
+            // was taken above
+            if (CHAIN && a.chain == 1 && !chain_ready) heuristic_step(a.ctrl, a.n, f, over ? 0 : (int32_t)off);
+            if (over) {
                 // Single vector: more products than stored entries means x
                 // has duplicate indices.  Batched: more products than the
                 // bucket storage holds.
@@ -370,6 +370,8 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
         }
     }
 
+    // the scan's decision after a pull level has reached every workgroup of it
+    if (a.gate && blockIdx.x == 0 && tid == 0) consume_chain(a.ctrl);
     if (a.gate && dir != 0) return;   // this BFS level runs pull
     // A failed look-back leaves the column tables inconsistent: scatter
     // nothing (the error is reported with the call's status).
@@ -712,7 +714,7 @@ __global__ __launch_bounds__(BLOCK, BATCH ? 8 : 1) void k_merge(MergeArgs a) {
     if (cnt_raw == 0) {
         // an empty tile writes its (empty) words of y's bitmap, and publishes
         // where its vector or the whole of y starts or ends
-        if (!BFS && !BATCH && a.y_bits)
+        if (!BATCH && a.y_bits)
             for (int w = tid; w < (rows + 31) >> 5; w += BLOCK) a.y_bits[(row0 >> 5) + w] = 0u;
         const bool last = b == a.nb - 1;
         if (tid < kWave && (last || (BATCH && bt == 0))) {
@@ -882,8 +884,8 @@ __global__ __launch_bounds__(BLOCK, BATCH ? 8 : 1) void k_merge(MergeArgs a) {
     if (!BATCH && (BFS || a.y_bits))
         for (int w = tid; w < nw; w += BLOCK) {
             const uint32_t bits = bm[w];
-            if (!BFS) a.y_bits[(row0 >> 5) + w] = bits;
-            else if (bits) visited[(row0 >> 5) + w] |= bits;
+            if (a.y_bits) a.y_bits[(row0 >> 5) + w] = bits;
+            if (BFS && bits) visited[(row0 >> 5) + w] |= bits;
         }
     if (BATCH && BFS)
         for (int w = tid; w < nw; w += BLOCK)
@@ -970,7 +972,7 @@ hipError_t launch_scan(const ScanArgs& a, int grid, hipStream_t s, const LaunchE
         return scan_mode<kScanItemsWide, true>(a, grid, s, ev);
     }
     if (a.chain) {
-        if (!a.f_dev || !a.xbits || (a.chain == 2 && !a.sel)) return hipErrorInvalidValue;
+        if (!a.f_dev || !a.chain_lbp || (a.chain == 2 && !a.sel)) return hipErrorInvalidValue;
         return scan_mode<kScanItemsWide, false, true>(a, grid, s, ev);
     }
     if (a.f_dev || a.wide) return scan_mode<kScanItemsWide, false>(a, grid, s, ev);
