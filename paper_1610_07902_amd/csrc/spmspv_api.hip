@@ -1122,7 +1122,10 @@ int enqueue_batch(spmspv_matrix* A, int semiring, int xmode, int nbatch, const i
         HIP_TRY(launch_exclusive_scan_i32(kcount, K + 1, i32(L.partials), s));
     }
     HIP_TRY(launch_scatter_batch(ca, semiring, sc.scatter_block, sc.scatter_items, (int)g2, false, s));
-    HIP_TRY(launch_merge_batch(ma, semiring, sc.merge_block, bfs, s));
+    // at most 512 threads: most keys are short and a second or third workgroup
+    // on the compute unit gives more than threads do (64 vectors 476 us with
+    // 1024, 452 with 512, 507 with 256; 64 searches 1654, 1580, 1585)
+    HIP_TRY(launch_merge_batch(ma, semiring, std::min(sc.merge_block, 512), bfs, s));
     return SPMSPV_OK;
 }
 

@@ -664,7 +664,8 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
 // publishes where its part starts (yoff).  Most keys of a batch are short and
 // wait behind long ones, so two workgroups share a compute unit: four entries
 // per thread (at most 64 registers) and the shorter list of merge_list_rows.
-// 64 vectors on a scale-20 graph: 302 us before, 245 now.
+// 64 vectors on a scale-20 graph: 302 us before, 245 with 1024 threads; 512 take
+// another 24 off the call.
 __device__ __forceinline__ void publish_total(const MergeArgs& a, int64_t total, bool batch) {
     a.ctrl->nnz_y = total;
     if (a.d_nnz_y) *a.d_nnz_y = total;
