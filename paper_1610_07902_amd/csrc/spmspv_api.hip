@@ -701,7 +701,16 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
             HIP_TRY(launch_hbm_merge(ma, semiring, bfs, s));
             if (ev) HIP_TRY(hipEventRecord(ev[5], s));
         } else {
-            HIP_TRY(launch_merge(ma, semiring, sc.merge_block, bfs, s, ev ? &le[2] : nullptr));
+            // A bucket of few entries leaves most of 1024 threads idle in its
+            // barriers and scans: at most 256 threads where the mean bucket of
+            // a call of known length expects 512 entries, 512 up to 2048 (a
+            // thread holds eight; past that the bucket takes the long way).
+            // Merge us with 1024 / 512 / 256 threads: 1 entry per bucket 8.0 /
+            // 7.0 / 6.4, 430 8.0 / 6.9 / 6.4, 1070 8.9 / 8.1 / 8.4, 2000 9.0 /
+            // 8.4 / 14.7, 5500 10.9 / 16.0 / 18.4.
+            const double mean = On > 0 ? (double)f_host * (double)A->nnz / (double)On / nb : 0.0;
+            const int most = f_dev || mean > 2048.0 ? 1024 : mean > 512.0 ? 512 : 256;
+            HIP_TRY(launch_merge(ma, semiring, std::min(sc.merge_block, most), bfs, s, ev ? &le[2] : nullptr));
         }
     }
     return SPMSPV_OK;

@@ -719,7 +719,7 @@ __global__ __launch_bounds__(BLOCK, BATCH ? 8 : 1) void k_merge(MergeArgs a) {
             for (int w = tid; w < (rows + 31) >> 5; w += BLOCK) a.y_bits[(row0 >> 5) + w] = 0u;
         const bool last = b == a.nb - 1;
         if (tid < kWave && (last || (BATCH && bt == 0))) {
-            const uint64_t e = lookback(a.lb3, b, 0ull, &a.ctrl->err, a.rep);
+            const uint64_t e = lookback<4>(a.lb3, b, 0ull, &a.ctrl->err, a.rep);
             if (tid == 0) {
                 if (BATCH && bt == 0) a.yoff[xb] = (int64_t)e;
                 if (last) publish_total(a, (int64_t)e, BATCH);

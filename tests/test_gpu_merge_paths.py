@@ -98,3 +98,19 @@ def test_batch_of_mixed_buckets(spv, semiring):
     for b, p in enumerate(parts):
         ref = oracle.spmspv(A, p, xv[off[b]:off[b + 1]], semiring)[:2]
         compare(semiring, yi[yo[b]:yo[b + 1]], yv[yo[b]:yo[b + 1]], *ref, sorted_output=True)
+
+
+@pytest.mark.parametrize("n", [30011, 200003])
+@pytest.mark.parametrize("semiring", [0, 1, 2])
+def test_long_bucket_among_short_ones(spv, n, semiring):
+    """274 buckets of 256 rows: the mean asks for fewer threads, the hub's bucket takes the long way."""
+    A = matrix(70001, n, 0.5)
+    M = spv.Matrix.from_csc(A)
+    s = M.schedule
+    s.tile_log2 = 8
+    M.schedule = s
+    rng = np.random.default_rng(semiring)
+    xi = rng.permutation(A.n).astype(np.int32)
+    xv = x_values(semiring, A.n, rng)
+    yi, yv, nnz = M.spmspv(torch.from_numpy(xi).cuda(), torch.from_numpy(xv).cuda(), semiring, True)
+    compare(semiring, yi[:nnz], yv[:nnz], *oracle.spmspv(A, xi, xv, semiring)[:2], sorted_output=True)
