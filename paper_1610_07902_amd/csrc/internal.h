@@ -340,7 +340,7 @@ hipError_t launch_scatter_batch(const ScatterArgs& a, int semiring, int block, i
 // packed into the bitmap and cleared, so `bytes` (at least 32 * ceil(m / 32)
 // bytes) is all zero before and after.
 hipError_t launch_mask_bits(const int32_t* idx, const uint8_t* val, int64_t count, int32_t m, uint8_t* bytes,
-                            uint32_t* bits, uint32_t* err, hipStream_t s);
+                            uint32_t* bits, uint32_t* err, uint64_t* lb, int lb_n, hipStream_t s);
 struct CombineArgs {
     const int32_t* t_idx;    // masked product, ascending
     const void* t_val;

@@ -1796,10 +1796,13 @@ int spmspv_run_graphblas(spmspv_handle A, int semiring, int flags, int64_t f, co
 
     // (1) the mask's rows as a bitmap (the BFS visited bitmap's storage)
     uint32_t* bits = nullptr;
+    uint64_t* const lb = reinterpret_cast<uint64_t*>(A->ws + A->L.gb_lb);   // the combine's look-back words
+    const int32_t lb_n = (int32_t)gb_lb_words(ylen);
     if (has_mask) {
         bits = A->visited;
         HIP_TRY(launch_mask_bits(mask_idx, mask_val, mask_count, (int32_t)ylen,
-                                 reinterpret_cast<uint8_t*>(A->ws + A->L.gb_bytes), bits, &A->ctrl->err, s));
+                                 reinterpret_cast<uint8_t*>(A->ws + A->L.gb_bytes), bits, &A->ctrl->err,
+                                 w_count > 0 ? lb : nullptr, lb_n, s));
     }
     // (2) t = A x restricted to the mask, ascending; straight into y when
     // there is nothing to accumulate into (then the result is t: rows
@@ -1843,10 +1846,10 @@ int spmspv_run_graphblas(spmspv_handle A, int semiring, int flags, int64_t f, co
         ca.y_cap = y_capacity;
         ca.d_nnz_y = d_nnz_y;
         ca.ctrl = A->ctrl;
-        ca.lb = reinterpret_cast<uint64_t*>(A->ws + A->L.gb_lb);
-        ca.lb_n = (int32_t)gb_lb_words(ylen);
+        ca.lb = lb;
+        ca.lb_n = lb_n;
         ca.rep = rep;
-        HIP_TRY(launch_clear_u64(ca.lb, ca.lb_n, s));
+        if (!has_mask) HIP_TRY(launch_clear_u64(ca.lb, ca.lb_n, s));
         int64_t grid = (ylen + w_count + kCombineTile - 1) / kCombineTile;
         if (grid < 1) grid = 1;
         // co-resident (four 33 KB workgroups fit one compute unit's LDS):
