@@ -359,7 +359,9 @@ int spmspv_last_stats(spmspv_handle A, int64_t* h_out, void* stream);
  * recorded events, writes the summed milliseconds of each phase
  * (0 = scan, 1 = bucket scatter, 2 = merge + compaction) to h_ms[3] and the
  * number of profiled calls to *h_calls, then clears the record.  A call
- * made in one launch records its kernel under phase 0 (1 and 2 stay 0).  */
+ * made in one launch records its kernel under phase 0 (1 and 2 stay 0);
+ * where scan and bucketing are one kernel (no column of more than 2047
+ * entries), it counts as phase 1 and phase 0 is the empty interval before. */
 int spmspv_profile_read(spmspv_handle A, double* h_ms, int64_t* h_calls);
 
 /* Release the handle (host memory and HIP events only; the caller frees
