@@ -56,6 +56,8 @@ __device__ __forceinline__ void comb_global(uint32_t* cell, uint32_t v) {
 // ---------------------------------------------------------------- x -> dense
 template <int XMODE>
 __global__ __launch_bounds__(256) void k_pull_prep(PullArgs a) {
+    // a multiply that runs push has no emit to clear the x bits again
+    if (a.gate && ldc(&a.ctrl->dir) != 1) return;
     const int f = a.f_dev ? ldc(a.f_dev) : a.f_host;
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.bump_level && f > 0) stc(&a.ctrl->level, ldc(&a.ctrl->level) + 1);
     // the emit look-back words of this call (the previous emit has finished)
