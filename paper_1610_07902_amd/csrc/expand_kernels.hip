@@ -49,6 +49,7 @@ static_assert(1024ll * kLongCol < (1ll << kSumBits), "packed scan");
 template <int BLOCK, int ITEMS, int SR, int XMODE>
 __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
     constexpr int C = BLOCK * ITEMS;
+    static_assert(C <= kExpandMaxChunk, "bound of the fill counters");
     constexpr int WORDS = C / 32;   // column-start bits of a chunk
     extern __shared__ __align__(16) uint32_t lds_expand[];
     const int nb = a.nb;
@@ -62,6 +63,7 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
     int32_t* const pre = reinterpret_cast<int32_t*>(bits + WORDS);              // [WORDS] columns before each word
     __shared__ int s_tmp[BLOCK / kWave + 1];
     __shared__ int s_base;
+    __shared__ int s_over;   // a run of this workgroup did not fit its bucket
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wid = tid / kWave;
@@ -75,6 +77,7 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
     }
     for (int i = tid; i < nb + kWave; i += BLOCK) hist[i] = 0;
     for (int i = tid; i < WORDS; i += BLOCK) bits[i] = 0u;
+    if (tid == 0) s_over = 0;
     const int tl = a.tile_log2;
     // x entries per tile: the host's choice, or for a device-known f the
     // widest tile that still gives every workgroup one
@@ -90,7 +93,9 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
         top = a.rcp[(int)min((int64_t)r0 + (int64_t(1) << tl), (int64_t)a.m)];
     }
 
-    // The products of `ncols` columns in the LDS table, `total` in all.
+    // The products of `ncols` columns in the LDS table, `total` in all.  After
+    // a run that did not fit (repeated x indices, reported) nothing more is
+    // added, which bounds the fill counters.
     auto bucket_products = [&](int ncols, int total) {
         if (tid == 0) s_base = 0;
         __syncthreads();   // the table and the cleared bits are written
@@ -214,8 +219,9 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
                 sort();
                 loaded(g);   // not before the sort
                 if (n > 0) {
-                    if (base + g[0] + n > top) {
+                    if (!slots_fit(g[0], n, top - base)) {
                         atomicOr(&a.ctrl->err, ERR_BUCKET_OVERFLOW);
+                        s_over = 1;
                         hist[b] = kNoSlot;
                     } else {
                         hist[b] = base + g[0];
@@ -236,8 +242,9 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
                             const int base = a.rcp[r0];
                             const int cap = a.rcp[(int)min((int64_t)r0 + (int64_t(1) << tl), (int64_t)a.m)] - base;
                             const int g = atomicAdd(&a.cursor[b], n);
-                            if (g + n > cap) {
+                            if (!slots_fit(g, n, cap)) {
                                 atomicOr(&a.ctrl->err, ERR_BUCKET_OVERFLOW);
+                                s_over = 1;
                                 hist[b] = kNoSlot;
                             } else {
                                 hist[b] = base + g;
@@ -273,6 +280,7 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
                 }
             }
             __syncthreads();
+            if (s_over) break;   // uniform: set before a barrier that every thread has passed
             for (int i = tid; i < nb; i += BLOCK) hist[i] = 0;
         }
     };
@@ -331,6 +339,7 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
         }
         bucket_products((int)((uint32_t)packed >> kSumBits), packed & ((1 << kSumBits) - 1));
         __syncthreads();   // the table is written again
+        if (s_over) break;
     }
     // this workgroup's share of the call's statistics (added up by the merge)
 #pragma unroll

@@ -35,8 +35,8 @@ __global__ __launch_bounds__(kHBlock) void k_hmerge_acc(MergeArgs a) {
     const int cap = a.rcp[row1] - a.rcp[row0];
     // slots past the bucket's capacity exist only after an overflow
     // (duplicate x indices): never read past the bucket
-    const int cnt = min(cnt_raw, cap);
-    if (cnt_raw > cap && part == 0 && threadIdx.x == 0) atomicOr(&a.ctrl->err, ERR_BUCKET_OVERFLOW);
+    const int cnt = (int)min((uint32_t)cnt_raw, (uint32_t)cap);
+    if (cnt != cnt_raw && part == 0 && threadIdx.x == 0) atomicOr(&a.ctrl->err, ERR_BUCKET_OVERFLOW);
     const int per = (cnt + a.h_split - 1) / a.h_split;
     const int e0 = part * per, e1 = min(cnt, e0 + per);
     bool bad = false;

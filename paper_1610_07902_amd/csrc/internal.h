@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "reserve.h"
+
 namespace spv {
 
 constexpr int kWave = 64;
@@ -182,7 +184,6 @@ struct ScatterArgs {
 
 // Expansion phase (scan and scatter in one kernel, expand_kernels.hip).
 constexpr int kLongCol = 2047;        // longest column it takes
-constexpr int kExpandMaxGrid = 4096;  // workgroups (entries of the statistics array)
 struct ExpandStat {
     int64_t products;   // sum of the lengths of the workgroup's selected columns
     int32_t columns;    // how many of them have entries

@@ -560,7 +560,7 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
             sort();
             loaded(g);   // not before the sort
             if (n > 0) {
-                if (base + g[0] + n > top) {
+                if (!slots_fit(g[0], n, top - base)) {
                     atomicOr(&a.ctrl->err, ERR_BUCKET_OVERFLOW);
                     hist[b] = -1;
                 } else {
@@ -588,7 +588,7 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
                             cap = a.rcp[(int)min((int64_t)r0 + (int64_t(1) << tl), (int64_t)a.m)] - kb;
                         }
                         const int g = atomicAdd(&a.cursor[b], n);
-                        if (g + n > cap) {
+                        if (!slots_fit(g, n, cap)) {
                             atomicOr(&a.ctrl->err, ERR_BUCKET_OVERFLOW);
                             hist[b] = -1;
                         } else {
@@ -732,7 +732,7 @@ __global__ __launch_bounds__(BLOCK, BATCH ? 8 : 1) void k_merge(MergeArgs a) {
     }
     // Slots past the bucket's capacity exist only after an overflow
     // (duplicate x indices); never read past the bucket.
-    const int cnt = min(cnt_raw, cap);
+    const int cnt = (int)min((uint32_t)cnt_raw, (uint32_t)cap);
     const int nw = (rows + 31) >> 5;
     const bool small = cnt <= BLOCK * ITEMS;
     // The first ITEMS entries per thread (all of a small bucket's), issued
