@@ -124,6 +124,7 @@ struct ScanArgs {
     int32_t* cursor;         // bucket fill counters, cleared here for scatter
     uint64_t* lb3;           // merge look-back words, cleared here
     int32_t nb;              // buckets of the current schedule
+    uint32_t refuse;         // error bits (of checks that the host has not read yet) that make x empty
     int bump_level;          // BFS: advance ctrl->level when f > 0
     int wide;                // 1: tiles of kScanItemsWide items per thread (large or device-known f)
     // Direction-switching BFS with the pull direction: 1 heuristic, 2

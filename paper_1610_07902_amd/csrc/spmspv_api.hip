@@ -331,6 +331,7 @@ struct spmspv_matrix {
     int32_t* front[2] = {nullptr, nullptr};
     int32_t* front2 = nullptr;          // connected components: the step's y indices
     int32_t maxdeg = 0;
+    bool unchecked = false;             // the host has not read the matrix checks' result (spmspv_run_static)
     int device = 0;
     int num_cu = 256;
     size_t lds_max = 65536;
@@ -558,6 +559,7 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
     sa.cursor = A->cursor;
     sa.lb3 = A->lb3;
     sa.nb = clear_nb > nb ? clear_nb : nb;
+    sa.refuse = A->unchecked ? ERR_CSC | ERR_ROW_RANGE : 0u;
     if (hbm && sa.nb < hmerge_tiles(Om)) sa.nb = (int32_t)hmerge_tiles(Om);   // its walk's look-back words
     sa.bump_level = bfs ? 1 : 0;
     // A direction-switching BFS level: after a pull level the scan takes the
@@ -608,7 +610,7 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
     int64_t g2 = (wbound + chunk - 1) / chunk;
     if (g2 < 1) g2 = 1;
     // scan and scatter in one kernel where no column is too long for its tiles
-    const bool fused = phases == 3 && !diropt && Omaxdeg <= kLongCol;
+    const bool fused = phases == 3 && !diropt && !A->unchecked && Omaxdeg <= kLongCol;
     if (!fused && (phases & 2))
         g2 = std::min(g2, int64_t(A->num_cu) *
                               scatter_occupancy(A, semiring, nb, sc.scatter_block, sc.scatter_items, false));
@@ -1902,14 +1904,17 @@ int spmspv_run_static(int64_t m, int64_t n, int64_t nnz, const int32_t* colptr, 
 
     // A handle on the stack over the scratch (no allocation: its host
     // containers stay empty), set up as spmspv_create sets one up, without
-    // the host read of the longest column (the bucketing grid is sized from
-    // nnz instead).
+    // the host read of the checks and of the longest column: the multiply's
+    // scan finds an empty x where a check failed (no column or row id of such
+    // a matrix is followed), the expansion, which relies on column lengths, is
+    // not taken, and the bucketing grid is sized from nnz.
     spmspv_matrix M;
     bind_workspace(&M, m, n, nnz, colptr, rowids, values, static_cast<char*>(ws), 0);
     M.device = dev;
     M.num_cu = info->num_cu;
     M.lds_max = info->lds_max;
     M.maxdeg = nnz > INT32_MAX ? INT32_MAX : (int32_t)nnz;
+    M.unchecked = true;
     default_schedule(&M, &M.sched);
     if ((rc = check_schedule(&M, &M.sched))) return fail(SPMSPV_EUNSUPPORTED, "matrix too tall for the LDS bucket layout");
     M.sched = sized_for_call(&M, f);

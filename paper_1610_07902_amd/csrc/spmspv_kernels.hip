@@ -72,6 +72,7 @@ __global__ __launch_bounds__(BLOCK) void k_scan(ScanArgs a) {
         f = ok ? (int)F : 0;
     } else {
         f = a.f_dev ? ld_ctrl(a.f_dev) : a.f_host;
+        if (a.refuse && ((uint32_t)ld_ctrl(reinterpret_cast<const int32_t*>(&a.ctrl->err)) & a.refuse)) f = 0;
     }
     // issued with the frontier length so the two round trips overlap
     uint32_t chain_ready = 0;
