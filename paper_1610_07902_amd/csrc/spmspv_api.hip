@@ -610,7 +610,10 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
     int64_t g2 = (wbound + chunk - 1) / chunk;
     if (g2 < 1) g2 = 1;
     // scan and scatter in one kernel where no column is too long for its tiles
-    const bool fused = phases == 3 && !diropt && !A->unchecked && Omaxdeg <= kLongCol;
+    // and its LDS, which is not the scatter's (the column table lies beside
+    // the sort buffer), fits too
+    const bool fused = phases == 3 && !diropt && !A->unchecked && Omaxdeg <= kLongCol &&
+                       expand_lds_bytes(nb, sc.scatter_block, sc.scatter_items) + 1024 <= A->lds_max;
     if (!fused && (phases & 2))
         g2 = std::min(g2, int64_t(A->num_cu) *
                               scatter_occupancy(A, semiring, nb, sc.scatter_block, sc.scatter_items, false));
