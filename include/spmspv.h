@@ -361,7 +361,8 @@ int spmspv_last_stats(spmspv_handle A, int64_t* h_out, void* stream);
  * number of profiled calls to *h_calls, then clears the record.  A call
  * made in one launch records its kernel under phase 0 (1 and 2 stay 0);
  * where scan and bucketing are one kernel (no column of more than 2047
- * entries), it counts as phase 1 and phase 0 is the empty interval before. */
+ * entries, and columns even enough for the call's size), it counts as phase 1
+ * and phase 0 is the empty interval before.                               */
 int spmspv_profile_read(spmspv_handle A, double* h_ms, int64_t* h_calls);
 
 /* Release the handle (host memory and HIP events only; the caller frees

@@ -13,9 +13,9 @@
 // touched bucket is reserved with one global atomic, and the chunk is
 // counting-sorted in LDS and written out in bucket runs.
 //
-// For matrices whose longest column has at most kLongCol entries: a tile then
-// holds at most a few chunks more than the others.  With longer columns the
-// two-kernel form's equal product chunks are the better split.  (Cutting long
+// For matrices whose columns are even enough that no tile holds many chunks
+// more than the others (expand_rule.h).  Else the two-kernel form's equal
+// product chunks are the better split.  (Cutting long
 // columns into queued pieces for idle or reserved workgroups was measured on
 // scale 22 at 1 %: 30 to 38 us against 30.5 for scan and scatter, the queue's
 // counters and waits costing what the scan did.)
@@ -30,6 +30,7 @@
 #include <hip/hip_ext.h>
 
 #include "device_ops.h"
+#include "expand_rule.h"
 
 #include <algorithm>
 #include <map>
@@ -80,9 +81,9 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
     if (tid == 0) s_over = 0;
     const int tl = a.tile_log2;
     // x entries per tile: the host's choice, or for a device-known f the
-    // widest tile that still gives every workgroup one
+    // widest tile within its bounds that still gives every workgroup one
     int per = a.per_tile;
-    if (a.f_dev) per = max(a.per_min, min(BLOCK, (f + (int)gridDim.x - 1) / (int)gridDim.x));
+    if (a.f_dev) per = max(a.per_min, min(a.per_max, (f + (int)gridDim.x - 1) / (int)gridDim.x));
     const int ntiles = (f + per - 1) / per;
 
     // the slots [base, top) of the bucket this thread reserves for
@@ -447,7 +448,7 @@ int expand_resident(int semiring, int xmode, int block, int items, int nb) {
 hipError_t launch_expand(const ExpandArgs& a, int semiring, int xmode, int block, int items, int grid, hipStream_t s,
                          const LaunchEvents* ev) {
     if (grid < 1 || grid > kExpandMaxGrid || a.per_tile < 1 || a.per_tile > block || a.per_min < 1 ||
-        a.per_min > block)
+        a.per_max < a.per_min || a.per_max > block)
         return hipErrorInvalidValue;
     const size_t lds = expand_lds_bytes(a.nb, block, items);
     return with_kernel(block, items, semiring, xmode, hipErrorInvalidValue, [&](auto kern) {

@@ -184,7 +184,6 @@ struct ScatterArgs {
 };
 
 // Expansion phase (scan and scatter in one kernel, expand_kernels.hip).
-constexpr int kLongCol = 2047;        // longest column it takes
 struct ExpandStat {
     int64_t products;   // sum of the lengths of the workgroup's selected columns
     int32_t columns;    // how many of them have entries
@@ -204,7 +203,8 @@ struct ExpandArgs {
     int32_t f_host;          // used when f_dev == nullptr
     const int32_t* f_dev;
     int32_t per_tile;        // x entries per workgroup tile (f_host)
-    int32_t per_min;         // at least that many for a device-known f
+    int32_t per_min;         // for a device-known f: at least and at most that many
+    int32_t per_max;
     Ctrl* ctrl;
     int bump_level;          // BFS: advance ctrl->level when f > 0
     int tile_log2;

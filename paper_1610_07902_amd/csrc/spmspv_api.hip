@@ -15,6 +15,7 @@
 #include <sstream>
 
 #include "spmspv.h"
+#include "expand_rule.h"
 #include "internal.h"
 
 using namespace spv;
@@ -471,28 +472,9 @@ int64_t scatter_occupancy(const spmspv_matrix* A, int semiring, int nb, int bloc
     return occ < 1 ? 1 : occ;
 }
 
-// How the expansion phase cuts f x entries into workgroup tiles.
-struct ExpandTiles {
-    int per;    // x entries per tile
-    int grid;   // workgroups
-};
-ExpandTiles expand_tiles(int64_t n, int64_t nnz, int64_t f, int block, int chunk, int gmax) {
-    const double d = std::max(1.0, n > 0 ? (double)nnz / (double)n : 1.0);   // products per x entry, on average
-    // one chunk's worth, with room for uneven columns
-    const int64_t one = std::max<int64_t>(1, (int64_t)(0.85 * chunk / d));
-    int64_t per = (f + gmax - 1) / gmax;                // a tile per workgroup
-    if (per > one) per = (per + one - 1) / one * one;   // or several chunks per tile
-    per = std::max<int64_t>(per, std::min<int64_t>(16, block));
-    per = std::min<int64_t>(per, block);
-    ExpandTiles t;
-    t.per = (int)per;
-    t.grid = (int)std::max<int64_t>(1, std::min<int64_t>((f + per - 1) / per, gmax));
-    return t;
-}
-
 // Enqueue the phases of one y <- A x: expansion and merge, or with columns too
-// long for the expansion or a decision in between (direction switching,
-// selector) scan, scatter and merge.
+// long or uneven for the expansion or a decision in between (direction
+// switching, selector) scan, scatter and merge.
 // phases: 1 = scan only, 2 = scatter + merge only (after a scan), 3 = all.  tile_log2 < 0
 // uses the handle's schedule.  clear_nb > 0 makes the scan clear that many
 // bucket counters (so a later scatter may use a narrower tile).
@@ -609,11 +591,18 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
     if (wbound > A->nnz) wbound = A->nnz;
     int64_t g2 = (wbound + chunk - 1) / chunk;
     if (g2 < 1) g2 = 1;
-    // scan and scatter in one kernel where no column is too long for its tiles
-    // and its LDS, which is not the scatter's (the column table lies beside
-    // the sort buffer), fits too
-    const bool fused = phases == 3 && !diropt && !A->unchecked && Omaxdeg <= kLongCol &&
-                       expand_lds_bytes(nb, sc.scatter_block, sc.scatter_items) + 1024 <= A->lds_max;
+    // scan and scatter in one kernel where the columns allow it and its LDS,
+    // which is not the scatter's (the column table lies beside the sort
+    // buffer), fits too
+    ExpandTiles et{};
+    if (phases == 3 && !diropt && !A->unchecked && Omaxdeg <= kLongCol &&
+        expand_lds_bytes(nb, sc.scatter_block, sc.scatter_items) + 1024 <= A->lds_max) {
+        const int gmax = (int)std::min<int64_t>(
+            kExpandMaxGrid,
+            (int64_t)A->num_cu * expand_resident(semiring, xmode, sc.scatter_block, sc.scatter_items, nb));
+        et = expand_tiles(On, A->nnz, Omaxdeg, f_dev ? -1 : f_host, sc.scatter_block, chunk, gmax);
+    }
+    const bool fused = et.taken;
     if (!fused && (phases & 2))
         g2 = std::min(g2, int64_t(A->num_cu) *
                               scatter_occupancy(A, semiring, nb, sc.scatter_block, sc.scatter_items, false));
@@ -677,20 +666,17 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
         // scratch of the one-launch multiply, which this call is not
         static_assert(size_t(kExpandMaxGrid) * sizeof(ExpandStat) <= size_t(kFMaxGrid) * kFSamples * 4, "stat array");
         ea.stat = reinterpret_cast<ExpandStat*>(A->ws + A->L.samples);
-        const int gmax = (int)std::min<int64_t>(
-            kExpandMaxGrid, (int64_t)A->num_cu * expand_resident(semiring, xmode, sc.scatter_block, sc.scatter_items, nb));
-        const ExpandTiles et = expand_tiles(On, A->nnz, f_host, sc.scatter_block, chunk, gmax);
         ea.per_tile = et.per;
-        ea.per_min = std::min(sc.scatter_block, 16);
-        const int grid = f_dev ? gmax : et.grid;
+        ea.per_min = et.per_min;
+        ea.per_max = et.per_max;
         ma.stat = ea.stat;
-        ma.stat_n = grid;
+        ma.stat_n = et.grid;
         ma.nnz = A->nnz;
         if (ev) {   // no scan kernel: its phase is the empty interval before this one
             HIP_TRY(hipEventRecord(ev[0], s));
             HIP_TRY(hipEventRecord(ev[1], s));
         }
-        HIP_TRY(launch_expand(ea, semiring, xmode, sc.scatter_block, sc.scatter_items, grid, s, ev ? &le[1] : nullptr));
+        HIP_TRY(launch_expand(ea, semiring, xmode, sc.scatter_block, sc.scatter_items, et.grid, s, ev ? &le[1] : nullptr));
         phases = 4;   // the merge is left
     }
     if (phases & 1) {
