@@ -8,6 +8,7 @@
 #include <string>
 #include <atomic>
 #include <mutex>
+#include <new>
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -234,8 +235,11 @@ BatchLayout make_batch_layout(int64_t m, int64_t n, int64_t nnz, int max_batch, 
 // Pinned host memory for what calls read back: one slot per handle, from slabs
 // shared by the process (pinning takes about 0.1 ms, as long as the rest of
 // a small create).  A slab other than the first goes back once all of its
-// slots are free.  The pool outlives the handles (it is never destroyed: a
-// handle may be closed while the process exits).
+// slots are free, with the next handle that is made: freeing pinned memory waits
+// for the GPU and is not allowed while a stream is being captured, and handles
+// are released at any time (by a garbage collector, for one).  The pool
+// outlives the handles (it is never destroyed: a handle may be closed while the
+// process exits).
 struct alignas(512) PinSlot {
     Ctrl ctrl;
     Report rep;
@@ -245,34 +249,27 @@ static_assert(sizeof(PinSlot) == 512, "two slots never share a cache line");
 
 class PinPool {
    public:
-    PinSlot* take() {
+    // nullptr: none to be had, the caller copies through pageable memory
+    PinSlot* take() noexcept {
         std::lock_guard<std::mutex> g(mu_);
-        for (auto& sl : slabs_)
-            if (!sl.free.empty()) return pop(sl);
-        void* p = nullptr;
-        if (hipHostMalloc(&p, kSlots * sizeof(PinSlot), hipHostMallocPortable) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;   // the caller copies through pageable memory
-        }
-        Slab sl;
-        sl.base = static_cast<PinSlot*>(p);
-        for (int k = kSlots; k-- > 0;) sl.free.push_back(sl.base + k);
-        slabs_.push_back(std::move(sl));
-        return pop(slabs_.back());
-    }
-    void give(PinSlot* s) {
-        if (!s) return;
-        std::lock_guard<std::mutex> g(mu_);
+        PinSlot* s = nullptr;
         for (size_t k = 0; k < slabs_.size(); ++k) {
             Slab& sl = slabs_[k];
-            if (s < sl.base || s >= sl.base + kSlots) continue;
-            sl.free.push_back(s);
-            if (k > 0 && sl.free.size() == (size_t)kSlots) {
+            if (!s && !sl.free.empty()) {
+                s = sl.free.back();
+                sl.free.pop_back();
+            } else if (k > 0 && sl.free.size() == (size_t)kSlots) {
                 (void)hipHostFree(sl.base);
-                slabs_.erase(slabs_.begin() + (std::ptrdiff_t)k);
+                slabs_.erase(slabs_.begin() + (std::ptrdiff_t)k--);
             }
-            return;
         }
+        return s ? s : grow();
+    }
+    void give(PinSlot* s) noexcept {
+        if (!s) return;
+        std::lock_guard<std::mutex> g(mu_);
+        for (auto& sl : slabs_)
+            if (s >= sl.base && s < sl.base + kSlots) sl.free.push_back(s);   // within what grow reserved
     }
 
    private:
@@ -281,10 +278,23 @@ class PinPool {
         PinSlot* base = nullptr;
         std::vector<PinSlot*> free;
     };
-    static PinSlot* pop(Slab& sl) {
-        PinSlot* s = sl.free.back();
-        sl.free.pop_back();
-        return s;
+    PinSlot* grow() noexcept {
+        try {   // host memory first: nothing is pinned when that runs out
+            slabs_.reserve(slabs_.size() + 1);
+            Slab sl;
+            sl.free.reserve(kSlots);
+            void* p = nullptr;
+            if (hipHostMalloc(&p, kSlots * sizeof(PinSlot), hipHostMallocPortable) != hipSuccess) {
+                (void)hipGetLastError();
+                return nullptr;
+            }
+            sl.base = static_cast<PinSlot*>(p);
+            for (int k = kSlots; k-- > 1;) sl.free.push_back(sl.base + k);
+            slabs_.push_back(std::move(sl));
+            return slabs_.back().base;
+        } catch (const std::bad_alloc&) {
+            return nullptr;
+        }
     }
     std::mutex mu_;
     std::vector<Slab> slabs_;
