@@ -337,8 +337,10 @@ int spmspv_autotune_batch(spmspv_handle A, int semiring, int flags, int nbatch, 
 /* Read / replace the launch schedule (NULL restores the default).  While
  * the default is in place, spmspv_run sizes the scatter chunk per call from
  * the expected product count f * nnz / n: the largest chunk, up to 4096
- * products, that still gives every compute unit one (see
- * spmspv_effective_schedule).                                             */
+ * products, that still gives every compute unit one, and the merge's
+ * workgroup from the products a bucket can expect (see
+ * spmspv_effective_schedule); batched calls merge with 512 threads.  A
+ * schedule that is set, tuned or loaded is used as it is.                  */
 int spmspv_get_schedule(spmspv_handle A, spmspv_schedule* h_sched);
 int spmspv_set_schedule(spmspv_handle A, const spmspv_schedule* h_sched);
 

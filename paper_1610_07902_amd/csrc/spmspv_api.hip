@@ -416,14 +416,37 @@ int default_schedule(const spmspv_matrix* A, spmspv_schedule* s) {
     return SPMSPV_OK;
 }
 
+// Tile one call merges with: the schedule's tile, narrowed for plus-times
+// (fp64 cells take twice the LDS of the other semirings' cells).
+int call_tile(const spmspv_matrix* A, int tl, int semiring) {
+    tl = tile_for(tl, semiring);
+    while (tl > kTileLog2Min && merge_lds_bytes(tl, semiring) + 1024 > A->lds_max) --tl;
+    return tl;
+}
+
+// Merge threads of a default schedule for f x entries (of n columns, the longest
+// of `longest` entries) in nb buckets.  A bucket of few entries leaves most of
+// 1024 threads idle in its barriers and scans.  What x lists is not known here:
+// 512 threads lose nothing that shows with the heaviest columns, 256 do, so
+// these are for calls in which no x brings a mean bucket more than 512 entries.
+// Whole calls in us with 256 / 512 / 1024 threads: 50 columns of a 64^3 grid
+// 29.7 / 30.1 / 31.2; scale 22, 4000 random columns (425 entries per bucket)
+// 42.3 / 42.2 / 42.9, the 4000 heaviest (110,000) 303 / 276 / 273; 15000 random
+// (1700) 55.0 / 49.7 / 50.2, the heaviest (194,000) 592 / 557 / 555.
+int merge_threads(int64_t n, int64_t nnz, int64_t longest, int64_t f, int64_t nb) {
+    const double per = n > 0 && nb > 0 ? (double)nnz / (double)n / (double)nb : 0.0;
+    const double most = nb > 0 ? std::min((double)f * (double)longest, (double)nnz) / (double)nb : 0.0;
+    return most <= 512.0 ? 256 : (double)f * per <= 2048.0 ? 512 : 1024;
+}
+
 // Default schedule for one standalone call with f x entries: the scatter
 // takes chunks of exactly block x items products, one workgroup per chunk
 // at a time, so with few products a large chunk leaves compute units idle.
 // Take the largest chunk (at most 4096 products: two workgroups per compute
 // unit overlap their phases; measured faster than 8192 at every density on
 // R-MAT scale 22) for which the expected product count f * nnz / n still
-// gives every compute unit one.
-spmspv_schedule sized_for_call(const spmspv_matrix* A, int64_t f) {
+// gives every compute unit one.  The merge's threads follow the call too.
+spmspv_schedule sized_for_call(const spmspv_matrix* A, int semiring, int64_t f) {
     spmspv_schedule s = A->sched;
     const double w_est = A->n > 0 ? (double)f * (double)A->nnz / (double)A->n : 0.0;
     const int64_t nb = (A->m + (int64_t(1) << s.tile_log2) - 1) >> s.tile_log2;
@@ -435,6 +458,16 @@ spmspv_schedule sized_for_call(const spmspv_matrix* A, int64_t f) {
         s.scatter_items = sh[1];
         if (w_est >= (double)chunk * A->num_cu) break;
     }
+    const int tl = call_tile(A, s.tile_log2, semiring);
+    s.merge_block = merge_threads(A->n, A->nnz, A->maxdeg, f, (A->m + (int64_t(1) << tl) - 1) >> tl);
+    return s;
+}
+
+// A left call's default: the handle's schedule, merge threads for A^T.
+spmspv_schedule sized_for_left(const spmspv_matrix* A, int semiring, int64_t f) {
+    spmspv_schedule s = A->sched;
+    const int tl = call_tile(A, s.tile_log2, semiring);
+    s.merge_block = merge_threads(A->m, A->nnz, A->maxrow, f, (A->n + (int64_t(1) << tl) - 1) >> tl);
     return s;
 }
 
@@ -458,14 +491,6 @@ int check_schedule(const spmspv_matrix* A, const spmspv_schedule* s) {
     if (scatter_lds_bytes((int)nb, sb * si) + 1024 > A->lds_max)
         return fail(SPMSPV_EINVAL, "too many buckets for the scatter LDS histogram");
     return SPMSPV_OK;
-}
-
-// Tile one call merges with: the schedule's tile, narrowed for plus-times
-// (fp64 cells take twice the LDS of the other semirings' cells).
-int call_tile(const spmspv_matrix* A, int tl, int semiring) {
-    tl = tile_for(tl, semiring);
-    while (tl > kTileLog2Min && merge_lds_bytes(tl, semiring) + 1024 > A->lds_max) --tl;
-    return tl;
 }
 
 // Bucketing workgroups one compute unit holds at once (registers, LDS and
@@ -702,16 +727,7 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
             HIP_TRY(launch_hbm_merge(ma, semiring, bfs, s));
             if (ev) HIP_TRY(hipEventRecord(ev[5], s));
         } else {
-            // A bucket of few entries leaves most of 1024 threads idle in its
-            // barriers and scans: at most 256 threads where the mean bucket of
-            // a call of known length expects 512 entries, 512 up to 2048 (a
-            // thread holds eight; past that the bucket takes the long way).
-            // Merge us with 1024 / 512 / 256 threads: 1 entry per bucket 8.0 /
-            // 7.0 / 6.4, 430 8.0 / 6.9 / 6.4, 1070 8.9 / 8.1 / 8.4, 2000 9.0 /
-            // 8.4 / 14.7, 5500 10.9 / 16.0 / 18.4.
-            const double mean = On > 0 ? (double)f_host * (double)A->nnz / (double)On / nb : 0.0;
-            const int most = f_dev || mean > 2048.0 ? 1024 : mean > 512.0 ? 512 : 256;
-            HIP_TRY(launch_merge(ma, semiring, std::min(sc.merge_block, most), bfs, s, ev ? &le[2] : nullptr));
+            HIP_TRY(launch_merge(ma, semiring, sc.merge_block, bfs, s, ev ? &le[2] : nullptr));
         }
     }
     return SPMSPV_OK;
@@ -974,8 +990,16 @@ int run_selected(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, cons
                             mask, false, false, s, nullptr);
     }
     const int c = h.cls < 9 ? h.cls : 8;
-    return enqueue(A, semiring, xmode, f_host, f_dev, x_idx, x_val, y_idx, y_val, y_cap, d_nnz_y, bfs, mask, s,
-                   nullptr, false, class_tile(A, c), 2, 0, false, 0, false, 0);
+    const int tl = class_tile(A, c);
+    const spmspv_schedule keep = A->sched;
+    if (A->sched_default && !f_dev) {
+        const int t = call_tile(A, tl, semiring);
+        A->sched.merge_block = merge_threads(A->n, A->nnz, A->maxdeg, f_host, (A->m + (int64_t(1) << t) - 1) >> t);
+    }
+    rc = enqueue(A, semiring, xmode, f_host, f_dev, x_idx, x_val, y_idx, y_val, y_cap, d_nnz_y, bfs, mask, s, nullptr,
+                 false, tl, 2, 0, false, 0, false, 0);
+    A->sched = keep;
+    return rc;
 }
 
 // Shape of a batched call: the narrowest tile at or above the handle's whose
@@ -983,6 +1007,12 @@ int run_selected(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, cons
 // LDS with one of the candidate workgroup shapes.
 int batch_shape(const spmspv_matrix* A, int nbatch, int semiring, spmspv_schedule* out) {
     spmspv_schedule sc = A->sched;
+    // By default 512 merge threads: most keys are short and a second or third
+    // workgroup on the compute unit gives more than threads do.  Scale 20 with
+    // 512 / 1024 threads: 64 vectors of 64 random columns 169 / 194 us, of 64 of
+    // the 256 heaviest 607 / 616, of 1024 of the 4096 heaviest 1624 / 1589;
+    // 64 searches 1580 / 1654.
+    if (A->sched_default) sc.merge_block = 512;
     if (A->batch_sched.tile_log2 > 0) sc = A->batch_sched;
     const int shapes[4][2] = {{sc.scatter_block, sc.scatter_items}, {1024, 4}, {512, 4}, {256, 4}};
     for (int tl = call_tile(A, sc.tile_log2, semiring); tl <= kTileLog2Max; ++tl) {
@@ -1132,10 +1162,7 @@ int enqueue_batch(spmspv_matrix* A, int semiring, int xmode, int nbatch, const i
         HIP_TRY(launch_exclusive_scan_i32(kcount, K + 1, i32(L.partials), s));
     }
     HIP_TRY(launch_scatter_batch(ca, semiring, sc.scatter_block, sc.scatter_items, (int)g2, false, s));
-    // at most 512 threads: most keys are short and a second or third workgroup
-    // on the compute unit gives more than threads do (64 vectors 476 us with
-    // 1024, 452 with 512, 507 with 256; 64 searches 1654, 1580, 1585)
-    HIP_TRY(launch_merge_batch(ma, semiring, std::min(sc.merge_block, 512), bfs, s));
+    HIP_TRY(launch_merge_batch(ma, semiring, sc.merge_block, bfs, s));
     return SPMSPV_OK;
 }
 
@@ -1554,7 +1581,7 @@ int spmspv_effective_schedule(spmspv_handle A, int semiring, int64_t f, int flag
     const spmspv_schedule keep = A->sched;
     const spmspv_schedule* tuned = (flags & SPMSPV_AUTO_SCHEDULE) ? tuned_for(A, f) : nullptr;
     if (tuned) A->sched = *tuned;
-    else if (A->sched_default) A->sched = sized_for_call(A, f);
+    else if (A->sched_default) A->sched = sized_for_call(A, semiring, f);
     spmspv_schedule e = A->sched;
     if (e.direction == 0) {
         if (e.merge_variant == 0) e.tile_log2 = call_tile(A, e.tile_log2, semiring);
@@ -1633,12 +1660,13 @@ int spmspv_run_masked(spmspv_handle A, int semiring, int flags, int64_t f, const
         if (flags & (SPMSPV_USE_SELECTOR | SPMSPV_PULL_ROWWISE))
             return fail(SPMSPV_EINVAL, "SPMSPV_DETERMINISTIC runs the push multiply only");
         const spmspv_schedule keep = A->sched;
-        if (A->sched_default && !left) A->sched = sized_for_call(A, f);
+        if (A->sched_default && !left) A->sched = sized_for_call(A, semiring, f);
         rc = enqueue_det(A, xmode, f, x_idx, x_val, y_idx, static_cast<float*>(y_val), y_capacity, d_nnz_y, mask, 0,
                          left, s, rep);
         A->sched = keep;
     } else if (left) {
         const spmspv_schedule keep = A->sched;
+        if (A->sched_default) A->sched = sized_for_left(A, semiring, f);
         A->sched.direction = 0;
         rc = enqueue(A, semiring, xmode, f, nullptr, x_idx, x_val, y_idx, y_val, y_capacity, d_nnz_y, false, mask, s,
                      ev, false, -1, 3, 0, false, 0, true, -1, nullptr, rep);
@@ -1653,7 +1681,7 @@ int spmspv_run_masked(spmspv_handle A, int semiring, int flags, int64_t f, const
         const spmspv_schedule keep = A->sched;
         const spmspv_schedule* tuned = (flags & SPMSPV_AUTO_SCHEDULE) ? tuned_for(A, f) : nullptr;
         if (tuned) A->sched = *tuned;
-        else if (A->sched_default) A->sched = sized_for_call(A, f);
+        else if (A->sched_default) A->sched = sized_for_call(A, semiring, f);
         int G = 0, ftl = 0, fnb = 0;
         if (A->sched.direction == 0 && A->sched.launch == 2) {
             G = A->dcsc ? 0 : fused_eligible(A, semiring, f, &ftl, &fnb);
@@ -1816,7 +1844,7 @@ int spmspv_run_graphblas(spmspv_handle A, int semiring, int flags, int64_t f, co
     Report* const rep = begin_report(A, h_nnz_y);
     Report* const t_rep = direct ? rep : nullptr;
     const spmspv_schedule keep = A->sched;
-    if (A->sched_default && !left) A->sched = sized_for_call(A, f);
+    if (A->sched_default) A->sched = left ? sized_for_left(A, semiring, f) : sized_for_call(A, semiring, f);
     A->sched.direction = 0;
     int rc;
     if (!has_mask && complement) {
@@ -1916,7 +1944,7 @@ int spmspv_run_static(int64_t m, int64_t n, int64_t nnz, const int32_t* colptr, 
     M.unchecked = true;
     default_schedule(&M, &M.sched);
     if ((rc = check_schedule(&M, &M.sched))) return fail(SPMSPV_EUNSUPPORTED, "matrix too tall for the LDS bucket layout");
-    M.sched = sized_for_call(&M, f);
+    M.sched = sized_for_call(&M, semiring, f);
     const Layout& L = M.L;
     // The scratch keeps the previous call's contents: clear the control block,
     // counters and look-back words (a fill kernel, not a memset).
