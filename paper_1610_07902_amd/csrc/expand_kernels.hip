@@ -80,10 +80,14 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
     for (int i = tid; i < WORDS; i += BLOCK) bits[i] = 0u;
     if (tid == 0) s_over = 0;
     const int tl = a.tile_log2;
-    // x entries per tile: the host's choice, or for a device-known f the
-    // widest tile within its bounds that still gives every workgroup one
+    // x entries per tile: the host's choice, or for a device-known f the same
+    // number of tiles for every workgroup, as few as the tiles' bounds allow
     int per = a.per_tile;
-    if (a.f_dev) per = max(a.per_min, min(a.per_max, (f + (int)gridDim.x - 1) / (int)gridDim.x));
+    if (a.f_dev) {
+        const int wide = (int)gridDim.x * a.per_max;   // of one round of tiles
+        const int all = (int)gridDim.x * max(1, (f + wide - 1) / wide);
+        per = max(a.per_min, (f + all - 1) / all);
+    }
     const int ntiles = (f + per - 1) / per;
 
     // the slots [base, top) of the bucket this thread reserves for
@@ -281,7 +285,7 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
                 }
             }
             __syncthreads();
-            if (s_over) break;   // uniform: set before a barrier that every thread has passed
+            if (q0 + C < total && s_over) break;   // uniform: set before a barrier that every thread has passed
             for (int i = tid; i < nb; i += BLOCK) hist[i] = 0;
         }
     };
@@ -340,7 +344,7 @@ __global__ __launch_bounds__(BLOCK) void k_expand(ExpandArgs a) {
         }
         bucket_products((int)((uint32_t)packed >> kSumBits), packed & ((1 << kSumBits) - 1));
         __syncthreads();   // the table is written again
-        if (s_over) break;
+        if (tile + (int)gridDim.x < ntiles && s_over) break;
     }
     // this workgroup's share of the call's statistics (added up by the merge)
 #pragma unroll

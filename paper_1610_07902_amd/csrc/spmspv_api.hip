@@ -635,7 +635,7 @@ int enqueue(spmspv_matrix* A, int semiring, int xmode, int64_t f_host, const int
         const int gmax = (int)std::min<int64_t>(
             kExpandMaxGrid,
             (int64_t)A->num_cu * expand_resident(semiring, xmode, sc.scatter_block, sc.scatter_items, nb));
-        et = expand_tiles(On, A->nnz, Omaxdeg, f_dev ? -1 : f_host, sc.scatter_block, chunk, gmax);
+        et = expand_tiles(On, A->nnz, Omaxdeg, f_dev ? -1 : f_host, sc.scatter_block, chunk, gmax, A->num_cu);
     }
     const bool fused = et.taken;
     if (!fused && (phases & 2))

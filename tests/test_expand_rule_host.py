@@ -1,7 +1,8 @@
 """CPU test of when the expansion takes a call and how it cuts it into tiles
 (csrc/expand_rule.h): over matrices from even to skewed, calls from one entry
 to all and every chunk shape, no choice of columns gives one workgroup's tile
-much more than its share, and even matrices are always taken."""
+much more than its share, even matrices are always taken, and tiles are neither
+thinner than a chunk where there are many nor thicker where there are few."""
 import os
 import subprocess
 
@@ -24,7 +25,8 @@ int main() {
                             const int64_t nnz = (int64_t)(mean * n);
                             if (f > n || longest * n < nnz || longest > nnz) continue;
                             const int block = sh[0], chunk = sh[0] * sh[1];
-                            const ExpandTiles t = expand_tiles(n, nnz, longest, f, block, chunk, gmax);
+                            const int cus = gmax < 256 ? gmax : 256;
+                            const ExpandTiles t = expand_tiles(n, nnz, longest, f, block, chunk, gmax, cus);
                             (t.taken ? taken : refused)++;
                             const double m = mean > 1.0 ? mean : 1.0;
                             if (t.taken && longest > 2047) FAIL("column of %lld taken\n", (long long)longest);
@@ -36,7 +38,8 @@ int main() {
                             const int64_t most_f = f < 0 ? n : f;
                             int64_t per = t.per;
                             if (f < 0) {
-                                per = (most_f + t.grid - 1) / t.grid;
+                                const int64_t wide = (int64_t)t.grid * t.per_max, rounds = (most_f + wide - 1) / wide;
+                                per = (most_f + t.grid * rounds - 1) / (t.grid * rounds);
                                 per = per > t.per_max ? t.per_max : per < t.per_min ? t.per_min : per;
                             }
                             const double extra = (double)per * longest - 2.0 * per * m;
@@ -44,9 +47,14 @@ int main() {
                                 FAIL("tile of %lld: longest %lld mean %g chunk %d f %lld\n", (long long)per,
                                      (long long)longest, mean, chunk, (long long)f);
                             const int64_t tiles = (most_f + per - 1) / per;
-                            // several tiles: each filled, or the whole workgroup wide
-                            if (tiles > t.grid && per < block && per * m < 0.8 * chunk - m)
+                            // several tiles: each filled (evenly dealt out by rounds: half filled at
+                            // least), or the whole workgroup wide
+                            if (tiles > (f < 0 ? t.grid : cus) && per < block &&
+                                per * m < (f < 0 ? 0.4 : 0.8) * chunk - m)
                                 FAIL("%lld thin tiles on %d workgroups\n", (long long)tiles, t.grid);
+                            // fewer tiles than compute units: none of more than a chunk, or of several columns
+                            if (f > 0 && tiles < cus / 2 && per > 1 && per * m > chunk)
+                                FAIL("%lld tiles of %g products\n", (long long)tiles, per * m);
                         }
     if (!taken || !refused) FAIL("taken %lld refused %lld\n", (long long)taken, (long long)refused);
     std::puts("ok");
