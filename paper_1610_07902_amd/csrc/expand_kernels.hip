@@ -25,7 +25,7 @@
 // three more to read the tables back.  Nothing here needs the products'
 // global positions: bucket slots are reserved, and the sums W needs are
 // written per workgroup and added up by the merge.  Measured on a 64^3 grid, 50
-// columns: scan 5.9 + scatter 5.6 us against 4.6 us.
+// columns: scan 7.9 + scatter 4.5 us against 5.3 us.
 
 #include <hip/hip_ext.h>
 

@@ -1,6 +1,7 @@
 // Hot-path kernels of SpMSpV-bucket for gfx950 (CDNA4, wave64).
 //
-// One y <- A x is three launches on one stream:
+// One y <- A x is three launches on one stream, two where the expansion
+// (expand_kernels.hip) takes steps (a) and (b) together:
 //   k_scan    (step a) gathers the selected columns' [colptr[j], colptr[j+1])
 //             ranges, prefix-sums their lengths with a single-pass
 //             decoupled look-back scan, compacts the non-empty columns and
@@ -16,16 +17,16 @@
 //             is reserved with one atomic per (chunk, bucket), which plays
 //             the role of Algorithm 2's per-thread Boffset prefix.
 //   k_merge   (steps c, d) gives each bucket one workgroup and an LDS-resident
-//             sparse accumulator over the bucket's rows.  Every cell of the
-//             tile is initialised with wide stores (on the GPU cheaper than
-//             the first-touch test that Algorithm 1's partial
-//             initialisation needs); touched rows are marked in an LDS row
-//             bitmap, whose population count is the bucket's number of
-//             unique rows.  The per-bucket unique
-//             counts are prefix-summed across workgroups by decoupled
-//             look-back, and each workgroup writes its rows straight to y
-//             (Algorithm 1, step 3), ascending when sorted output is asked
-//             for (walk of the row bitmap in order).
+//             sparse accumulator over the bucket's rows.  A bucket whose
+//             entries fit the workgroup's registers clears only the cells of
+//             their rows (Algorithm 1's partial initialisation); a longer one
+//             initialises the whole tile with wide stores, on the GPU cheaper
+//             than a first-touch test per entry.  Touched rows are marked in
+//             an LDS row bitmap, whose population count is the bucket's
+//             number of unique rows.  The per-bucket unique counts are
+//             prefix-summed across workgroups by decoupled look-back, and each
+//             workgroup writes its rows straight to y (Algorithm 1, step 3),
+//             ascending (walk of the row bitmap in order).
 //
 // Bucket storage: bucket k covers rows [k*T, (k+1)*T) with T = 2^tile_log2.
 // Its slots start at rcp[k*T], the number of stored entries of A in rows
@@ -655,9 +656,10 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(ScatterArgs a) {
 // bucket 15.4 us before, 10.3 now (launch and first loads 2.4, rows 1.2, count
 // and adds 1.9, look-back 2.4, writes 0.6); with 50,500 entries 39 before, 33
 // now.  The LDS bounds the latter: its fp64 adds retire 2 lanes per cycle, 10.5
-// us for the mean bucket and 14 for the longest; without hub sums 43 (one row
-// of the longest bucket has 16,000 of its 67,000 entries), with two rows in
-// registers instead of one 43 as well (conversions and adds of every entry).
+// us for the mean bucket and 14 for the longest; without hub sums 38.5 (one row
+// of the longest bucket has 16,000 of its 67,000 entries), and two rows in
+// registers instead of one cost more than they save (conversions and adds of
+// every entry).
 //
 // Batched calls (BATCH): workgroup k merges key k = vector * nbx + bucket;
 // the look-back runs over all keys, so y holds the vectors' results one
