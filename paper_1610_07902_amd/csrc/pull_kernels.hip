@@ -377,19 +377,23 @@ __global__ __launch_bounds__(256) void k_pull_bfs(PullArgs a) {
 }
 
 // -------------------------------------------------------------- emit y
-// Walks ybits in order, kEmitWords words per workgroup, and writes y with a
+// Walks ybits in order, kEmitWords words per workgroup (emit_words), and writes y with a
 // decoupled look-back for the offsets.  Resets ybits / ydense for the next
 // call and clears the x bits this call set; in a direction-switching BFS it
 // writes the new frontier over the x bits instead and leaves per-workgroup
 // sums of its column lengths for the next level's decision.
 // Bound by the gathers per listed row (column ends, value) and its scattered
-// stores: one bitmap word per thread and four rows in flight each.  With 1024
-// words per workgroup a scale-22 graph had 128 workgroups of four waves and a
-// level of 1.6 million rows took 56.6 us; with 256 words, 26.0.
+// stores: one or two bitmap words per thread and four rows in flight each.  With
+// 1024 words per workgroup a scale-22 graph had 128 workgroups of four waves and
+// a level of 1.6 million rows took 56.6 us; with 256 words, 26.0.  Where 512
+// words still give every compute unit a workgroup, the shorter look-back is
+// worth more: a pull multiply of 16.8M rows with 256 / 512 / 1024 words 364 / 356
+// / 355 us for one x entry and 1068 / 1034 / 1035 for half of x; of 4.1M rows
+// 96 / 94 / 93 and 226 / 229 / 251; a search of scale 23 617 / 609 / 608.
 constexpr int kEmitBlock = 256;
-constexpr int kEmitWords = 256;
+inline int emit_words(int32_t m) { return m >= 512 * 32 * 256 ? 512 : 256; }
 
-template <int SR, bool BFS>
+template <int SR, bool BFS, int kEmitWords>
 __global__ __launch_bounds__(kEmitBlock) void k_emit(PullArgs a) {
     __shared__ int s_tmp[kEmitBlock / 64 + 1];
     __shared__ uint16_t s_list[kEmitWords * 32];
@@ -590,6 +594,23 @@ __global__ void k_check_sorted(const int32_t* colptr, const int32_t* rowids, int
 
 }  // namespace
 
+template <int WORDS>
+static hipError_t launch_emit(const PullArgs& a, int semiring, bool bfs, hipStream_t s) {
+    const dim3 ge(a.emit_blocks), be(kEmitBlock);
+    switch (semiring) {
+        case SR_PLUS_TIMES: hipLaunchKernelGGL((k_emit<SR_PLUS_TIMES, false, WORDS>), ge, be, 0, s, a); break;
+        case SR_MIN_SELECT2ND:
+            if (bfs) hipLaunchKernelGGL((k_emit<SR_MIN_SELECT2ND, true, WORDS>), ge, be, 0, s, a);
+            else hipLaunchKernelGGL((k_emit<SR_MIN_SELECT2ND, false, WORDS>), ge, be, 0, s, a);
+            break;
+        default:
+            if (bfs) hipLaunchKernelGGL((k_emit<SR_OR_AND, true, WORDS>), ge, be, 0, s, a);
+            else hipLaunchKernelGGL((k_emit<SR_OR_AND, false, WORDS>), ge, be, 0, s, a);
+            break;
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_pull(const PullArgs& a, int semiring, int xmode, bool bfs, bool early, bool rowwise,
                        hipStream_t s) {
     if (rowwise && semiring == SR_PLUS_TIMES) return hipErrorInvalidValue;
@@ -624,19 +645,7 @@ hipError_t launch_pull(const PullArgs& a, int semiring, int xmode, bool bfs, boo
             default: hipLaunchKernelGGL((k_pull<kPullBlock, kPullItems, SR_OR_AND>), g, b, 0, s, a); break;
         }
     }
-    const dim3 ge(a.emit_blocks), be(kEmitBlock);
-    switch (semiring) {
-        case SR_PLUS_TIMES: hipLaunchKernelGGL((k_emit<SR_PLUS_TIMES, false>), ge, be, 0, s, a); break;
-        case SR_MIN_SELECT2ND:
-            if (bfs) hipLaunchKernelGGL((k_emit<SR_MIN_SELECT2ND, true>), ge, be, 0, s, a);
-            else hipLaunchKernelGGL((k_emit<SR_MIN_SELECT2ND, false>), ge, be, 0, s, a);
-            break;
-        default:
-            if (bfs) hipLaunchKernelGGL((k_emit<SR_OR_AND, true>), ge, be, 0, s, a);
-            else hipLaunchKernelGGL((k_emit<SR_OR_AND, false>), ge, be, 0, s, a);
-            break;
-    }
-    return hipGetLastError();
+    return emit_words(a.m) == 512 ? launch_emit<512>(a, semiring, bfs, s) : launch_emit<256>(a, semiring, bfs, s);
 }
 
 hipError_t launch_clear_u64(uint64_t* p, int n, hipStream_t s) {
@@ -650,7 +659,10 @@ hipError_t launch_fill_ident(uint32_t* p, uint32_t v, int64_t n, hipStream_t s) 
     return hipGetLastError();
 }
 
-int pull_emit_blocks(int32_t m) { return ((m + 31) / 32 + kEmitWords - 1) / kEmitWords; }
+int pull_emit_blocks(int32_t m) {
+    const int words = emit_words(m);
+    return (int)((((int64_t)m + 31) / 32 + words - 1) / words);
+}
 int pull_blocks(int32_t m, int64_t nnz) { return (int)(((int64_t)m + nnz + kPullChunk - 1) / kPullChunk); }
 
 hipError_t launch_pull_setup(const int32_t* colptr, const int32_t* rowids, const float* values, int32_t m,
